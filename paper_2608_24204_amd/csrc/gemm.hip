@@ -280,6 +280,10 @@ constexpr int kDmaStages = 2;
 __device__ __forceinline__ void dma16(const bf16_t* g, bf16_t* lds_wave) {
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds_wave, 16, 0, 0);
 }
+// 4 bytes a lane
+__device__ __forceinline__ void dma4(const void* g, bf16_t* lds_wave) {
+  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds_wave, 4, 0, 0);
+}
 // s_waitcnt with vmcnt <= VM, lgkmcnt 0, expcnt unconstrained (gfx9 encoding)
 template <int VM>
 __device__ __forceinline__ void wait_vm_lgkm() {
@@ -516,18 +520,25 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(const bf16_t* __restrict__ 
 }
 
 // ------------------------------------------------- few rows, staged through LDS
-// The same product for at most 32 rows, bf16 weights, K a multiple of 128: a
-// workgroup owns 64 weight rows (16 per wavefront) and walks its K range in
-// 128-deep slices through a ring of kRowsStages LDS stages, the weight slice
-// (64 rows x 256 bytes) and the activation slice (NT planes x 16 TM rows x 256
-// bytes) fetched by global_load_lds_dwordx4 in whole 128-byte lines, sixteen
-// lanes to a row.  (Fragment-shaped loads straight into registers touch sixteen
-// rows per instruction, 64 bytes each, and stream no faster than ~4.9 TB/s.)
-// The 16-byte chunks of a row are XOR-swizzled by the row's low bits, so a
-// fragment read (sixteen rows, one chunk) covers all 64 banks once.
+// The same product for up to 16 TM rows, K a multiple of 128: bound by streaming
+// W.  A workgroup owns 64 WN weight rows (16 WN per wavefront) and all rows of A,
+// and walks its K range in KC-deep slices through a ring of STG LDS stages, the
+// weight slice and the activation slice (NT planes x 16 TM rows) fetched by
+// global_load_lds_dwordx4 in whole 128-byte lines.  (Fragment-shaped loads
+// straight into registers touch sixteen rows per instruction, 64 bytes each, and
+// stream no faster than ~4.9 TB/s.)  The 16-byte chunks of a row are
+// XOR-swizzled by the row's low bits, so a fragment read (sixteen rows, one
+// chunk) covers all 64 banks once.
+//
+// Q8 weights: the slice holds the codes as they are (half the bytes); each
+// fragment belongs to one wavefront, which converts its eight codes per lane to
+// exact bf16 integers on the way into the matrix cores, sums a 32-deep block's
+// NT products in a fresh accumulator and adds it times the block's scale (the
+// lane's column).  A slice's scales go through LDS with its stage (in registers
+// the compiler waited for every load in flight before each slice).
 //
 // Products with few weight rows are split along K over grid slots: the splits
-// of a 64-row tile occupy workgroup indices of one residue mod 8, so they run on
+// of a tile occupy workgroup indices of one residue mod 8, so they run on
 // one XCD (dispatch deals workgroups to the XCDs in turn) and exchange their
 // partials through its L2, as the decode attention merge does: each split
 // stores its accumulators, waits for the L2 to acknowledge them, records its
@@ -535,103 +546,228 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(const bf16_t* __restrict__ 
 // L1, adds the partials in split order (so the sum does not depend on timing),
 // applies the epilogue and resets the counter.  A split that ran elsewhere
 // sets *fault.
-constexpr int kRowsKC = 128;     // K per LDS stage
-constexpr int kRowsStages = 3;   // two slices in flight while one is multiplied
-static_assert(kRowsStages >= 2 && kRowsStages <= 4, "stage ring of 2-4");
+constexpr int kRowsKC = 128;       // K ranges are multiples of this (whole slices)
 constexpr int kRowsSyncLine = 64;  // ints per tile: counter at 0, XCD records from 32
 constexpr int kRowsMaxTiles = kGemmRowsSyncInts / kRowsSyncLine;  // tiles that can be split
+// Rows the kernel takes: while it beats the 128-row tiles of the prefill products.
+constexpr int kRowsMaxBf16 = 128, kRowsMaxQ8 = 64;
 
-template <int NT, int TM, int EPI>
-__global__ __launch_bounds__(256) void k_gemm_rows(const bf16_t* __restrict__ A, size_t a_plane,
-                                                   int lda, const bf16_t* __restrict__ W, int M,
+// LDS chunk (16 bytes) of a row's chunk c, for rows of CH chunks: rows of 256 bytes
+// all start at bank 0, rows of 128 bytes alternate between two halves.
+template <int CH>
+__device__ __forceinline__ int rows_swz(int row, int c) {
+  return CH == 16 ? c ^ (row & 15) : c ^ ((row >> 1) & 7);
+}
+
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+// Two LDS dwords, as a plain vector load: a load through a struct (uint2) or a bit
+// cast carries no type information, and the compiler then waits for every
+// direct-to-LDS load in flight first (s_waitcnt vmcnt(0), which empties the ring).
+__device__ __forceinline__ u32x2_t lds_b64(const bf16_t* p) {
+  const u32x2_t v = *reinterpret_cast<const u32x2_t*>(p);
+  return v;
+}
+
+// 8 codes (q + 128) as 8 bf16 values q, exact: with its top bit flipped a code byte
+// is q in two's complement, which one instruction converts to fp32 (byte select and
+// sign extension included); the upper halves of two of those are the bf16 pair.
+__device__ __forceinline__ bf16x8_t q8_frag(u32x2_t c) {
+  unsigned o[4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int w = (int)(c[h] ^ 0x80808080u);
+    const float f0 = (float)(int8_t)w, f1 = (float)(int8_t)(w >> 8);
+    const float f2 = (float)(int8_t)(w >> 16), f3 = (float)(w >> 24);
+    o[2 * h] = __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302u);
+    o[2 * h + 1] = __builtin_amdgcn_perm(__float_as_uint(f3), __float_as_uint(f2), 0x07060302u);
+  }
+  return __builtin_bit_cast(bf16x8_t, make_uint4(o[0], o[1], o[2], o[3]));
+}
+
+template <int NT, int TM, int WN, int KC, int STG, int EPI, bool Q8>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_rows(const bf16_t* __restrict__ A, size_t a_plane,
+                                                   int lda, const void* __restrict__ Wv, int M,
                                                    int N, int K, int nsplit, int ks,
                                                    float* __restrict__ C, int ldc, ActBuf H,
                                                    int ldh, floatx4_t* __restrict__ part,
                                                    int* __restrict__ sync,
-                                                   int* __restrict__ fault, int drill) {
-  constexpr int CH = kRowsKC / 8;                 // 16-byte chunks per row of a slice
-  constexpr int WUNITS = 64 * CH;                 // weight units (16 bytes) per slice
-  constexpr int XUNITS = NT * 16 * TM * CH;       // activation units per slice
-  constexpr int PL = (WUNITS + XUNITS) / 256;     // units per lane per slice
-  constexpr int STAGE = (WUNITS + XUNITS) * 8;    // bf16 elements per stage
-  static_assert((WUNITS + XUNITS) % 256 == 0, "whole instructions per slice");
+                                                   int* __restrict__ fault, int drill,
+                                                   const unsigned short* __restrict__ S) {
+  constexpr int BN = 64 * WN;
+  constexpr int CHA = KC / 8;                      // 16-byte chunks per activation row
+  constexpr int CHW = Q8 ? KC / 16 : KC / 8;       // and per weight row
+  constexpr int WUNITS = BN * CHW;                 // weight units (16 bytes) per slice
+  // activation units per slice, whole instructions (the last units may be padding)
+  constexpr int XUNITS = (NT * 16 * TM * CHA + 255) / 256 * 256;
+  constexpr int PL = (WUNITS + XUNITS) / 256;      // units per lane per slice
+  constexpr int SUNITS = Q8 ? 64 : 0;              // Q8: 256 dwords of block scales
+  constexpr int STAGE = (WUNITS + XUNITS + SUNITS) * 8;  // bf16 elements per stage
+  constexpr int VM = PL + (Q8 ? 1 : 0);            // vector-memory operations per slice
+  static_assert(kRowsKC % KC == 0 && (CHA == 8 || CHA == 16) && (CHW == 8 || CHW == 16), "slices");
+  static_assert(!Q8 || (KC == 128 && WN <= 2), "four block scales per row and slice");
+  static_assert(STG >= 2 && STG <= 4, "stage ring of 2-4");
+  constexpr int SG = KC / kBK <= 2 || NT * TM <= 6 ? KC / kBK : 2;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
 
-  const int T = (N + 63) / 64;
+  const int T = (N + BN - 1) / BN;
   const int loc = blockIdx.x / 8;
   const int t = blockIdx.x % 8 + 8 * (loc / nsplit), split = loc % nsplit;
   if (t >= T) return;
-  const int n0 = t * 64, kbeg = split * ks;
+  const int n0 = t * BN, kbeg = split * ks;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
 
-  // unit u = (i * 4 + wave) * 64 + lane of a stage: weight row u / CH for u <
-  // WUNITS, else activation plane / row; its LDS chunk u % CH holds the row's
-  // global chunk (u % CH) ^ (row & (CH - 1))
-  const bf16_t* src[PL];
+  // unit u = (i * 4 + wave) * 64 + lane of a stage: weight row u / CHW for u <
+  // WUNITS, else activation plane / row; its LDS chunk holds the row's global
+  // chunk of the same swizzle (an involution)
+  const char* src[PL];
+  constexpr int WI = WUNITS / 256;                 // weight units of a lane come first
+  static_assert(WUNITS % 256 == 0, "a lane's unit i is weights or activations for every lane");
 #pragma unroll
   for (int i = 0; i < PL; ++i) {
     const int u = (i * 4 + wave) * 64 + lane;
-    if (u < WUNITS) {
-      const int r = u / CH, c = (u % CH) ^ (r & (CH - 1));
-      src[i] = W + (size_t)min(n0 + r, N - 1) * K + kbeg + c * 8;
+    if (i < WI) {
+      const int r = u / CHW, c = rows_swz<CHW>(r, u % CHW);
+      src[i] = static_cast<const char*>(Wv) +
+               ((size_t)min(n0 + r, N - 1) * K + kbeg) * (Q8 ? 1 : 2) + c * 16;
     } else {
-      const int v = u - WUNITS, p = v / (16 * TM * CH), r = (v / CH) % (16 * TM);
-      const int c = (v % CH) ^ (r & (CH - 1));
-      src[i] = A + p * a_plane + (size_t)min(r, M - 1) * lda + kbeg + c * 8;
+      const int v = u - WUNITS, p = min(v / (16 * TM * CHA), NT - 1), r = (v / CHA) % (16 * TM);
+      const int c = rows_swz<CHA>(r, v % CHA);
+      src[i] = reinterpret_cast<const char*>(A + p * a_plane + (size_t)min(r, M - 1) * lda + kbeg) +
+               c * 16;
     }
   }
+  const int fr = lane & 15, g = lane >> 4;
+  // Q8: lane tid fetches dword tid % 2 of weight row tid / 2's scales (four halves
+  // per slice); past the tile's rows the last row's again
+  const unsigned short* ssrc = nullptr;
+  if constexpr (Q8)
+    ssrc = S + (size_t)min(n0 + min(tid >> 1, BN - 1), N - 1) * (K / 32) + kbeg / 32 + 2 * (tid & 1);
   // Each workgroup starts its walk at its own slice and wraps around: in lockstep
   // every workgroup would read the same K offset of rows 8 KB apart, which
   // crowds a few HBM channels.  Offsets of 7 slices between the workgroups of
   // an XCD and 4 between XCDs measured best (a bare stream of the 8B gate/up
   // weights: 5.2 -> 6.0 TB/s; offsets of 1 slice: 4.2).
-  const int KT = ks / kRowsKC;
+  const int KT = ks / KC;
   const int rot = ((blockIdx.x / 8) * 7 + (blockIdx.x % 8) * 4) % KT;
   auto issue = [&](int stage, int kt) {
     bf16_t* sb = smem + stage * STAGE;
     const int kk = kt + rot < KT ? kt + rot : kt + rot - KT;
 #pragma unroll
-    for (int i = 0; i < PL; ++i) dma16(src[i] + kk * kRowsKC, sb + (i * 4 + wave) * 512);
+    for (int i = 0; i < PL; ++i)
+      dma16(reinterpret_cast<const bf16_t*>(src[i] + (size_t)kk * KC * (Q8 && i < WI ? 1 : 2)),
+            sb + (i * 4 + wave) * 512);
+    if constexpr (Q8) dma4(ssrc + kk * (KC / 32), sb + (WUNITS + XUNITS) * 8 + wave * 128);
   };
 
-  floatx4_t acc[TM];
+  floatx4_t acc[TM][WN];
 #pragma unroll
-  for (int i = 0; i < TM; ++i) acc[i] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  const int fr = lane & 15, g = lane >> 4;
+  for (int i = 0; i < TM; ++i)
 #pragma unroll
-  for (int s = 0; s < kRowsStages - 1; ++s)
+    for (int j = 0; j < WN; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](int stage) {
+    const bf16_t* sb = smem + stage * STAGE;
+    const bf16_t* xb = sb + WUNITS * 8;
+    u32x2_t sc[WN];
+    if constexpr (Q8) {
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+        sc[j] = lds_b64(sb + (WUNITS + XUNITS) * 8 + ((wave * WN + j) * 16 + fr) * 4);
+    }
+    // the slice's 32-deep steps in groups of SG: a group's fragment reads are issued
+    // together, and its products are independent chains
+#pragma unroll
+    for (int s0 = 0; s0 < KC / kBK; s0 += SG) {
+      u32x2_t wq[SG][WN];
+      bf16x8_t wf[SG][WN], xf[SG][TM][NT];
+#pragma unroll
+      for (int u = 0; u < SG; ++u) {
+        const int st = s0 + u;
+#pragma unroll
+        for (int j = 0; j < WN; ++j) {
+          const int wr = (wave * WN + j) * 16 + fr;
+          if constexpr (Q8)  // 8 codes: half of chunk 2 st + g / 2
+            wq[u][j] = lds_b64(sb + (wr * CHW + rows_swz<CHW>(wr, 2 * st + (g >> 1))) * 8 +
+                               4 * (g & 1));
+          else
+            wf[u][j] = *reinterpret_cast<const bf16x8_t*>(
+                sb + (wr * CHW + rows_swz<CHW>(wr, 4 * st + g)) * 8);
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int p = 0; p < NT; ++p) {
+            const int xr = i * 16 + fr;
+            xf[u][i][p] = *reinterpret_cast<const bf16x8_t*>(
+                xb + ((p * 16 * TM + xr) * CHA + rows_swz<CHA>(xr, 4 * st + g)) * 8);
+          }
+      }
+#pragma unroll
+      for (int u = 0; u < SG; ++u) {
+        if constexpr (Q8) {
+#pragma unroll
+          for (int j = 0; j < WN; ++j) wf[u][j] = q8_frag(wq[u][j]);
+        }
+      }
+      floatx4_t q[SG][TM][WN];
+      if constexpr (Q8) {
+#pragma unroll
+        for (int p = 0; p < NT; ++p)
+#pragma unroll
+          for (int u = 0; u < SG; ++u)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int j = 0; j < WN; ++j)
+                q[u][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    xf[u][i][p], wf[u][j], p ? q[u][i][j] : floatx4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+        for (int u = 0; u < SG; ++u)
+#pragma unroll
+          for (int j = 0; j < WN; ++j) {
+            const int st = s0 + u;
+            const unsigned w = st < 2 ? sc[j].x : sc[j].y;
+            const float d =
+                (float)__builtin_bit_cast(_Float16, (unsigned short)(st & 1 ? w >> 16 : w & 0xffffu));
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) acc[i][j][r] += q[u][i][j][r] * d;
+          }
+      } else {
+#pragma unroll
+        for (int u = 0; u < SG; ++u)
+#pragma unroll
+          for (int p = 0; p < NT; ++p)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+              for (int j = 0; j < WN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[u][i][p], wf[u][j], acc[i][j],
+                                                                    0, 0, 0);
+      }
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < STG - 1; ++s)
     if (s < KT) issue(s, s);
   for (int kt = 0; kt < KT; ++kt) {
-    const int ahead = min(kRowsStages - 2, KT - 1 - kt);  // later slices already issued
-    if (ahead >= 2) wait_vm_lgkm<2 * PL>();
-    else if (ahead == 1) wait_vm_lgkm<PL>();
+    const int ahead = min(STG - 2, KT - 1 - kt);  // later slices already issued
+    if (ahead >= 2) wait_vm_lgkm<2 * VM>();
+    else if (ahead == 1) wait_vm_lgkm<VM>();
     else wait_vm_lgkm<0>();
     __builtin_amdgcn_s_barrier();
-    if (kt + kRowsStages - 1 < KT) issue((kt + kRowsStages - 1) % kRowsStages, kt + kRowsStages - 1);
-    const bf16_t* sb = smem + (kt % kRowsStages) * STAGE;
-    const bf16_t* xb = sb + WUNITS * 8;
-#pragma unroll
-    for (int st = 0; st < kRowsKC / kBK; ++st) {
-      const int c = 4 * st + g;  // this lane's chunk of the 32-deep step
-      const int wr = wave * 16 + fr;
-      const bf16x8_t wf = *reinterpret_cast<const bf16x8_t*>(sb + (wr * CH + (c ^ (wr & (CH - 1)))) * 8);
-#pragma unroll
-      for (int p = 0; p < NT; ++p)
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int xr = i * 16 + fr;
-          const bf16x8_t xf = *reinterpret_cast<const bf16x8_t*>(
-              xb + ((p * 16 * TM + xr) * CH + (c ^ (xr & (CH - 1)))) * 8);
-          acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, wf, acc[i], 0, 0, 0);
-        }
-    }
+    if (kt + STG - 1 < KT) issue((kt + STG - 1) % STG, kt + STG - 1);
+    compute(kt % STG);
   }
 
   if (nsplit > 1) {
     __shared__ int s_last;
-    floatx4_t* slab = part + ((size_t)(t * nsplit + split) * 4 * TM + wave * TM) * 64;
+    constexpr int FR = TM * WN;  // accumulator tiles of a wavefront
+    floatx4_t* slab = part + ((size_t)(t * nsplit + split) * 4 + wave) * FR * 64;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) slab[i * 64 + lane] = acc[i];
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) slab[(i * WN + j) * 64 + lane] = acc[i][j];
     const int me = xcc_id();
     int* line = sync + (size_t)t * kRowsSyncLine;
     if (tid == 0) line[32 + split] = me;
@@ -653,33 +789,61 @@ __global__ __launch_bounds__(256) void k_gemm_rows(const bf16_t* __restrict__ A,
     // stores); the loads below also bypass it (sc0)
     asm volatile("buffer_inv sc0" ::: "memory");
     const __amdgpu_buffer_rsrc_t rp =
-        rsrc(part + (size_t)t * nsplit * 4 * TM * 64, (size_t)nsplit * 4 * TM * 64 * 16);
+        rsrc(part + (size_t)t * nsplit * 4 * FR * 64, (size_t)nsplit * 4 * FR * 64 * 16);
     const __amdgpu_buffer_rsrc_t rs = rsrc(line, kRowsSyncLine * 4);
     if (wave == 0 && lane < nsplit) {
       const int xo = __builtin_amdgcn_raw_buffer_load_b32(rs, (32 + lane) * 4, 0, 1);
       if (xo != me || drill) *fault = 1;
     }
+    floatx4_t sum[TM][WN];
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      floatx4_t sum = floatx4_t{0.f, 0.f, 0.f, 0.f};
-      for (int sp = 0; sp < nsplit; ++sp) {
-        const u32x4_t v = load_l2(rp, (int)((((size_t)sp * 4 * TM + wave * TM + i) * 64 + lane) * 16));
-        sum[0] += __uint_as_float(v.x); sum[1] += __uint_as_float(v.y);
-        sum[2] += __uint_as_float(v.z); sum[3] += __uint_as_float(v.w);
-      }
-      acc[i] = sum;
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) sum[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+    // the partials of SU splits are in flight together (past the last split the last
+    // one's again, not added)
+    constexpr int SU = FR <= 2 ? 8 : FR <= 4 ? 4 : 2;
+    for (int s0 = 0; s0 < nsplit; s0 += SU) {
+      u32x4_t v[SU][TM][WN];
+#pragma unroll
+      for (int u = 0; u < SU; ++u)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < WN; ++j)
+            v[u][i][j] = load_l2(rp, (int)((((size_t)min(s0 + u, nsplit - 1) * 4 + wave) * FR +
+                                            i * WN + j) * 64 + lane) * 16);
+#pragma unroll
+      for (int u = 0; u < SU; ++u)
+        if (s0 + u < nsplit) {
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j) {
+              sum[i][j][0] += __uint_as_float(v[u][i][j].x);
+              sum[i][j][1] += __uint_as_float(v[u][i][j].y);
+              sum[i][j][2] += __uint_as_float(v[u][i][j].z);
+              sum[i][j][3] += __uint_as_float(v[u][i][j].w);
+            }
+        }
     }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) acc[i][j] = sum[i][j];
   }
-  // epilogue (lane: rows 16 i + 4 g + r, column n0 + 16 wave + fr)
+  // epilogue (lane: rows 16 i + 4 g + r, column n0 + 16 (WN wave + j) + fr)
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = i * 16 + 4 * g + r, n = n0 + wave * 16 + fr;
-      const float v = acc[i][r];
-      const float o = EPI == GEMV_SWIGLU ? pair_swap(v) : 0.f;
-      epi_out<EPI>(C, ldc, H, ldh, M, N, m, n, v, o);
-    }
+    for (int j = 0; j < WN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = i * 16 + 4 * g + r, n = n0 + (wave * WN + j) * 16 + fr;
+        const float v = acc[i][j][r];
+        const float o = EPI == GEMV_SWIGLU ? pair_swap(v) : 0.f;
+        epi_out<EPI>(C, ldc, H, ldh, M, N, m, n, v, o);
+      }
 }
 
 // ------------------------------------------------------------------- vector fp32
@@ -851,21 +1015,27 @@ static hipError_t gemm_skinny(const ActBuf& A, int lda, const void* W, int M, in
 #undef WICI_SKT
 }
 
-template <int NT, int TM, int EPI>
+template <int NT, int TM, int WN, int KC, int STG, int EPI, bool Q8>
 static hipError_t gemm_rows_launch(const ActBuf& A, int lda, const void* W, int M, int N, int K,
                                    int nsplit, float* C, int ldc, const ActBuf& H, int ldh,
                                    float* part, int* sync, int* fault, hipStream_t st,
                                    int drill = 0) {
-  const int T = (N + 63) / 64;
+  const int T = (N + 64 * WN - 1) / (64 * WN);
   const int grid = 8 * ((T + 7) / 8) * nsplit;
-  const size_t lds = (size_t)kRowsStages * (64 + NT * 16 * TM) * kRowsKC * sizeof(bf16_t);
-  auto fn = &k_gemm_rows<NT, TM, EPI>;
+  const size_t lds =
+      (size_t)STG * (64 * WN * (Q8 ? 1 : 2) * KC + (NT * 16 * TM * 2 * KC + 4095) / 4096 * 4096 +
+                     (Q8 ? 1024 : 0));
+  const unsigned short* S =
+      Q8 ? reinterpret_cast<const unsigned short*>(static_cast<const char*>(W) +
+                                                   q8_scale_offset(N, K))
+         : nullptr;
+  auto fn = &k_gemm_rows<NT, TM, WN, KC, STG, EPI, Q8>;
   if (lds >= 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(fn, dim3(grid), dim3(256), lds, st, A.planes, A.plane_stride, lda,
-                     static_cast<const bf16_t*>(W), M, N, K, nsplit, K / nsplit, C, ldc, H, ldh,
-                     reinterpret_cast<floatx4_t*>(part), sync, fault, drill);
+  hipLaunchKernelGGL(fn, dim3(grid), dim3(256), lds, st, A.planes, A.plane_stride, lda, W, M, N, K,
+                     nsplit, K / nsplit, C, ldc, H, ldh, reinterpret_cast<floatx4_t*>(part), sync,
+                     fault, drill, S);
   return hipGetLastError();
 }
 
@@ -921,38 +1091,86 @@ hipError_t launch_gemm_split(int wt, const ActBuf& A, int lda, const void* W, in
 }
 
 // Splits along K for the few-rows kernel: the fewest (up to 16) that give at
-// least 192 workgroups with whole 128-deep slices, as far as the partials fit
-// `part_floats` and the tiles the sync lines.  (Measured at 16 rows on the 8B
-// shapes: QKV 2 splits 13.7 us, 4 17.3; O 4 splits 10.6 us, 8 12.1; down 4
-// splits 25.5 us, 7 28.6: more, shorter workgroups pay more in pipeline fill
-// and in the sum.)
-int gemm_rows_splits(int M, int N, int K, size_t part_floats) {
-  const int T = (N + 63) / 64, TM = M <= 16 ? 1 : 2;
+// least 192 workgroups of bn weight rows with whole 128-deep slices, as far as the
+// partials (tm 16-row tiles) fit `part_floats` and the tiles the sync lines.
+// (Measured at 16 rows on the 8B shapes, bf16: QKV 2 splits 12.6 us, 4 13.3; O 4
+// splits 9.9 us, 8 10.3; down 4 splits 24.8 us, 7 27.3; at 48 rows QKV 2 splits
+// 19.1 us, 8 20.0: more, shorter workgroups pay more in pipeline fill and in the
+// sum.)
+static int gemm_rows_splits(int tm, int bn, int N, int K, size_t part_floats) {
+  const int T = (N + bn - 1) / bn;
   if (T > kRowsMaxTiles) return 1;
   int best = 1;
   for (int s = 2; s <= 16 && T * best < 192; ++s) {
     if (K % (s * kRowsKC)) continue;
-    if ((size_t)T * s * 4 * TM * 64 * 4 > part_floats) break;
+    if ((size_t)T * s * bn * 16 * tm > part_floats) break;
     best = s;
   }
   return best;
+}
+
+// The launch shapes of the few-rows kernel: TM 16-row tiles, 64 WN weight rows per
+// workgroup, KC-deep slices in STG stages.
+template <int TM_, int WN_, int KC_, int STG_>
+struct RowsShape {
+  static constexpr int TM = TM_, WN = WN_, KC = KC_, STG = STG_;
+};
+
+template <int NT, int EPI, bool Q8>
+static hipError_t gemm_rows(const ActBuf& A, int lda, const void* W, int M, int N, int K, float* C,
+                            int ldc, const ActBuf& H, int ldh, float* part, size_t part_floats,
+                            int* sync, int* fault, hipStream_t st, bool drill) {
+  auto go = [&](auto shape) {
+    using R = decltype(shape);
+    const int nsplit = part && sync && fault
+                           ? gemm_rows_splits(R::TM, 64 * R::WN, N, K, part_floats) : 1;
+    return gemm_rows_launch<NT, R::TM, R::WN, R::KC, R::STG, EPI, Q8>(
+        A, lda, W, M, N, K, nsplit, C, ldc, H, ldh, part, sync, fault, st, drill);
+  };
+  // 128 weight rows per workgroup (each activation fragment read for twice the
+  // columns) where that alone still gives 192 workgroups: 8B gate/up, bf16, 43.2 ->
+  // 40.2 us at 16 rows, 49.2 -> 42.7 at 32, 55.5 -> 47.4 at 48, 62.3 -> 55.1 at 64;
+  // Q8 43.8 -> 39.6 at 32 and 78 -> 66 at 64, but 31.8 -> 33.3 at 8 and 47.8 -> 49.5
+  // at 48.  Narrower products keep 64 (O at 48 rows 15.6 against 17.9 us).  Slices
+  // are 128 deep up to 32 rows and 64 from 33 on (48 rows: gate/up 60.5 us at 128),
+  // the stages as many as leave two workgroups per CU, or one with wide slices.
+  const bool wide = EPI != GEMV_RESID && N >= 192 * 128;
+  if constexpr (Q8) {
+    if (M <= 16) return go(RowsShape<1, 1, 128, 4>{});
+    if (M <= 32) return wide ? go(RowsShape<2, 2, 128, 3>{}) : go(RowsShape<2, 1, 128, 3>{});
+    if (M <= 48) return go(RowsShape<3, 1, 128, 2>{});
+    return wide ? go(RowsShape<4, 2, 128, NT <= 2 ? 3 : 2>{}) : go(RowsShape<4, 1, 128, 2>{});
+  } else {
+    if (M <= 16) return wide ? go(RowsShape<1, 2, 128, 3>{}) : go(RowsShape<1, 1, 128, 3>{});
+    if (M <= 32) return wide ? go(RowsShape<2, 2, 64, 4>{}) : go(RowsShape<2, 1, 128, 3>{});
+    if (M <= 48) return wide ? go(RowsShape<3, 2, 64, 3>{}) : go(RowsShape<3, 1, 64, 3>{});
+    if (M <= 64) return wide ? go(RowsShape<4, 2, 64, 3>{}) : go(RowsShape<4, 1, 64, 3>{});
+    if (M <= 96) return go(RowsShape<6, 2, 64, 3>{});
+    return go(RowsShape<8, 2, 64, 2>{});
+  }
+}
+
+bool gemm_rows_takes(int wt, int nt, int M, int K) {
+  return nt >= 1 && nt <= 3 && M >= 1 && K % kRowsKC == 0 &&
+         ((wt == W_BF16 && M <= kRowsMaxBf16) || (wt == W_Q8 && M <= kRowsMaxQ8));
 }
 
 hipError_t launch_gemm_rows(int wt, int epi, const ActBuf& A, int lda, const void* W, int M,
                             int N, int K, float* C, int ldc, const ActBuf& H, int ldh,
                             float* part, size_t part_floats, int* sync, int* fault,
                             hipStream_t st, bool drill) {
-  if (wt != W_BF16 || A.nt < 1 || A.nt > 3 || M < 1 || M > 32 || K % kRowsKC)
+  if (!gemm_rows_takes(wt, A.nt, M, K))
     return launch_gemm(wt, epi, A, lda, W, M, N, K, C, ldc, H, ldh, st);
-  const int nsplit = part && sync && fault ? gemm_rows_splits(M, N, K, part_floats) : 1;
-#define WICI_RW(NT_, TM_, E) \
-  gemm_rows_launch<NT_, TM_, E>(A, lda, W, M, N, K, nsplit, C, ldc, H, ldh, part, sync, fault, st, \
-                                drill)
-#define WICI_RW_NT(E)                                                        \
-  switch (A.nt) {                                                            \
-    case 1: return M <= 16 ? WICI_RW(1, 1, E) : WICI_RW(1, 2, E);            \
-    case 2: return M <= 16 ? WICI_RW(2, 1, E) : WICI_RW(2, 2, E);            \
-    default: return M <= 16 ? WICI_RW(3, 1, E) : WICI_RW(3, 2, E);           \
+#define WICI_RW(NT_, E)                                                                         \
+  return wt == W_Q8 ? gemm_rows<NT_, E, true>(A, lda, W, M, N, K, C, ldc, H, ldh, part,         \
+                                              part_floats, sync, fault, st, drill)              \
+                    : gemm_rows<NT_, E, false>(A, lda, W, M, N, K, C, ldc, H, ldh, part,        \
+                                               part_floats, sync, fault, st, drill)
+#define WICI_RW_NT(E)            \
+  switch (A.nt) {                \
+    case 1: WICI_RW(1, E);       \
+    case 2: WICI_RW(2, E);       \
+    default: WICI_RW(3, E);      \
   }
   switch (epi) {
     case GEMV_STORE: WICI_RW_NT(GEMV_STORE)

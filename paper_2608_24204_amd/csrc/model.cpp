@@ -409,13 +409,27 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
   // (in split order, so the result does not depend on scheduling).
   float* P = m->S<float>(L.kpart);
   const size_t p_split = C * d;
-  const int s_o = wici::gemm_split_count(wb, rd(att, pl.o).nt, T, d, qd, kMaxKSplit);
-  const int s_d = wici::gemm_split_count(wb, rd(h, pl.down).nt, T, d, F, kMaxKSplit);
+  // Few rows: the weight-streaming products, which add their K ranges in the launch
+  // (P holds the partials; a misplaced range is reported through the state).
+  int* gsync = m->S<int>(L.gemm_sync);
+  int* gfault = &reinterpret_cast<DecodeState*>(m->ds + L.state)->fault;
+  auto prod = [&](int epi, const wici::ActBuf& in, int K, size_t w, int N, float* out, int ldo,
+                  const wici::ActBuf& hout, int ldh) {
+    return wici::gemm_rows_takes(wb, in.nt, T, K)
+               ? wici::launch_gemm_rows(wb, epi, in, K, m->dw + w, T, N, K, out, ldo, hout, ldh, P,
+                                        (size_t)kMaxKSplit * C * d, gsync, gfault, s)
+               : wici::launch_gemm(wb, epi, in, K, m->dw + w, T, N, K, out, ldo, hout, ldh, s);
+  };
+  auto splits = [&](int terms, int N, int K, int most) {
+    return wici::gemm_rows_takes(wb, terms, T, K)
+               ? 1 : wici::gemm_split_count(wb, terms, T, N, K, most);
+  };
+  const int s_o = splits(rd(att, pl.o).nt, d, qd, kMaxKSplit);
+  const int s_d = splits(rd(h, pl.down).nt, d, F, kMaxKSplit);
   // the QKV projection too, as far as its partials fit the split buffer; they are
   // added (in range order) by the RoPE + append kernel.  Measured at 1024 rows
   // (8B): 185 -> 164 us; at 512 rows (1B): 56 -> 33 us.
-  const int s_q = wici::gemm_split_count(wb, rd(a, pl.qkv).nt, T, nqkv, d,
-                                         std::min(kMaxKSplit, kMaxKSplit * d / nqkv));
+  const int s_q = splits(rd(a, pl.qkv).nt, nqkv, d, std::min(kMaxKSplit, kMaxKSplit * d / nqkv));
   const size_t q_split = C * nqkv;
   int pending = 0;  // splits of the previous down product not yet added to x
   // (the normalised rows are written with as many terms as their product reads)
@@ -428,8 +442,7 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
   auto resid = [&](const wici::ActBuf& in, int K, size_t w, int nsplit) {
     return nsplit > 1 ? wici::launch_gemm_split(wb, in, K, m->dw + w, T, d, K, nsplit, P, p_split,
                                                 s)
-                      : wici::launch_gemm(wb, wici::GEMV_RESID, in, K, m->dw + w, T, d, K, x, d,
-                                          none, 0, s);
+                      : prod(wici::GEMV_RESID, in, K, w, d, x, d, none, 0);
   };
   for (int l = 0; l < c.n_layers; ++l) {
     if ((e = norm(m->W<float>(m->layer(l, L.l_anorm)), pending, pl.qkv))) return e;
@@ -437,9 +450,8 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
       if ((e = wici::launch_gemm_split(wb, rd(a, pl.qkv), d, m->dw + m->layer(l, L.l_wqkv), T,
                                        nqkv, d, s_q, P, q_split, s)))
         return e;
-    } else if ((e = wici::launch_gemm(wb, wici::GEMV_STORE, rd(a, pl.qkv), d,
-                                      m->dw + m->layer(l, L.l_wqkv), T, nqkv, d, qkv, nqkv, none,
-                                      0, s))) {
+    } else if ((e = prod(wici::GEMV_STORE, rd(a, pl.qkv), d, m->layer(l, L.l_wqkv), nqkv, qkv,
+                         nqkv, none, 0))) {
       return e;
     }
     if ((e = wici::launch_rope_append(kb, qkv, T, p0, c.n_heads, m->W<float>(L.rope_cos),
@@ -450,8 +462,8 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
       return e;
     if ((e = resid(rd(att, pl.o), qd, m->layer(l, L.l_wo), s_o))) return e;
     if ((e = norm(m->W<float>(m->layer(l, L.l_fnorm)), s_o, pl.gu))) return e;
-    if ((e = wici::launch_gemm(wb, wici::GEMV_SWIGLU, rd(a, pl.gu), d,
-                               m->dw + m->layer(l, L.l_wgu), T, 2 * F, d, nullptr, 0, h, F, s)))
+    if ((e = prod(wici::GEMV_SWIGLU, rd(a, pl.gu), d, m->layer(l, L.l_wgu), 2 * F, nullptr, 0, h,
+                  F)))
       return e;
     if ((e = resid(rd(h, pl.down), F, m->layer(l, L.l_wdown), s_d))) return e;
     pending = s_d;

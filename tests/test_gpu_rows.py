@@ -1,0 +1,103 @@
+"""The few-row products (short prompts and batched decode steps) at the edges of
+their row tiles and launch shapes, bf16 and 8-bit weights, against the float64
+oracle: logits, and every cached key and value of every row.
+
+Tolerances: logits 1e-3 of the largest (fp32-accurate activations).  A cached key
+or value that lies next to a rounding boundary may round the other way, one bf16
+step, at most 2^-7 of it; a row in which every element did would be 2^-7 off in
+two-norm, a row or column a tile missed or took twice is of order one off."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from oracle import DecoderOracle, q8_model_f64
+from paper_2608_24204_amd import configs, inputs
+from tests.helpers import inf_rel
+
+pytestmark = pytest.mark.gpu
+
+# narrow: every product split along K (3 and 9 ranges of 128 among them), vocab and
+# QKV rows no multiple of a tile; wide: gate/up and LM head past 192 x 128 rows, the
+# LM head's last tile ragged
+CFGS = {
+    "narrow": configs.ModelConfig(name="t_rows", key=110, n_layers=2, d_model=384, n_heads=4,
+                                  n_kv_heads=2, head_dim=64, ffn_dim=1152, vocab=1003),
+    "wide": configs.ModelConfig(name="t_rows_wide", key=111, n_layers=2, d_model=256, n_heads=2,
+                                n_kv_heads=1, head_dim=128, ffn_dim=12416, vocab=24601),
+}
+
+
+def setup(name, weights):
+    cfg = CFGS[name].with_(weight_dtype=weights)
+    w = inputs.make_weights(cfg, gain_std=0.1)
+    return cfg, w, (q8_model_f64(w) if weights == "q8" else inputs.weights_f64(cfg, w))
+
+
+def check_kv(m, orc, n):
+    for l in range(m.cfg.n_layers):
+        for got, ref in zip(m.read_kv(l, 0, n), (orc.K[l][:n], orc.V[l][:n])):
+            got = inputs.bf16_bits_to_f32(got).astype(np.float64).reshape(n, -1)
+            ref = ref.reshape(n, -1)
+            err = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
+            assert err.max() <= 2.0 ** -7, (l, int(err.argmax()), float(err.max()))
+
+
+@pytest.mark.parametrize("weights", ["bf16", "q8"])
+@pytest.mark.parametrize("name", list(CFGS))
+def test_short_prompts_match_oracle(cuda_ok, name, weights):
+    """Prompts of 1 to 129 rows: both sides of every row tile, and of the most rows
+    the kernel takes (64 with 8-bit weights, 128 with bf16)."""
+    from paper_2608_24204_amd.binding import WiciModel
+    cfg, w, w64 = setup(name, weights)
+    sizes = [1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 96, 97, 128, 129]
+    toks = np.random.default_rng(3).integers(0, cfg.vocab, sizes[-1]).astype(np.int32)
+    orc = DecoderOracle(cfg, w64, max_seq=sizes[-1])
+    ref = orc.full(toks)
+    m = WiciModel(cfg, max_seq=sizes[-1])
+    try:
+        m.load_weights(w)
+        for n in sizes:
+            m.reset_kv()
+            tok, lg = m.prefill(toks[:n], want_logits=True)
+            print(f"[rows] {name} {weights} {n} rows: {inf_rel(lg, ref[n - 1]):.2e}", flush=True)
+            assert inf_rel(lg, ref[n - 1]) <= 1e-3, n
+            assert tok == int(np.argmax(lg)), n
+            check_kv(m, orc, n)
+    finally:
+        m.close()
+
+
+@pytest.mark.parametrize("weights", ["bf16", "q8"])
+@pytest.mark.parametrize("name,n", [("narrow", 9), ("narrow", 17), ("narrow", 48), ("narrow", 64),
+                                    ("narrow", 65), ("narrow", 130), ("wide", 3), ("wide", 49)])
+def test_batches_match_oracle(cuda_ok, name, weights, n):
+    """Batched steps with given tokens, sequences of different lengths."""
+    from paper_2608_24204_amd.binding import WiciModel
+    cfg, w, w64 = setup(name, weights)
+    rng = np.random.default_rng(n)
+    kw = dict(max_seq=40, prefill_chunk=256)
+    lead = WiciModel(cfg, **kw)
+    ms = [lead]
+    try:
+        lead.load_weights(w)
+        ms += [WiciModel(cfg, share_weights_of=lead, **kw) for _ in range(n - 1)]
+        ps = [rng.integers(0, cfg.vocab, 1 + b % 7).astype(np.int32) for b in range(n)]
+        fed = rng.integers(0, cfg.vocab, (2, n)).astype(np.int32)
+        for m, p in zip(ms, ps):
+            m.prefill(p)
+        lead.decode_batch(ms, fed[0])
+        toks, lg = lead.decode_batch(ms, fed[1], want_logits=True)
+        worst = 0.0
+        for b in range(n):
+            orc = DecoderOracle(cfg, w64, max_seq=40)
+            ref = orc.forward(np.concatenate([ps[b], fed[:, b]]))
+            worst = max(worst, inf_rel(lg[b], ref))
+            assert inf_rel(lg[b], ref) <= 1e-3, b
+            assert toks[b] == int(np.argmax(lg[b]))
+            check_kv(ms[b], orc, len(ps[b]) + 2)
+        print(f"[rows] {name} {weights} batch {n}: {worst:.2e}", flush=True)
+    finally:
+        for m in ms:
+            m.close()
