@@ -147,6 +147,29 @@ __device__ __forceinline__ void store_act4(const ActBuf& a, size_t idx, float4 v
   }
 }
 
+// Eight consecutive values (idx a multiple of 8): 16 bytes per plane.
+__device__ __forceinline__ void store_act8(const ActBuf& a, size_t idx, const float (&v)[8]) {
+  if (a.nt == 0) {
+    *reinterpret_cast<float4*>(a.f32 + idx) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<float4*>(a.f32 + idx + 4) = make_float4(v[4], v[5], v[6], v[7]);
+    return;
+  }
+  float r[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) r[e] = v[e];
+  for (int p = 0; p < a.nt; ++p) {
+    uint32_t o[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bf16_t lo = f32_to_bf16(r[2 * e]), hi = f32_to_bf16(r[2 * e + 1]);
+      r[2 * e] -= bf16_to_f32(lo);
+      r[2 * e + 1] -= bf16_to_f32(hi);
+      o[e] = (uint32_t)lo | ((uint32_t)hi << 16);
+    }
+    *reinterpret_cast<uint4*>(a.planes + p * a.plane_stride + idx) = make_uint4(o[0], o[1], o[2], o[3]);
+  }
+}
+
 // Greedy-argmax order: larger value wins, lower index wins among equal values.
 __device__ __forceinline__ bool am_better(float v, int i, float bv, int bi) {
   return v > bv || (v == bv && i < bi);

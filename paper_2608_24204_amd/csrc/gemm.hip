@@ -258,25 +258,30 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(
 }
 
 // --------------------------------------------------------- MFMA, direct to LDS
-// bf16 weights: a K step's tiles go from global memory straight into LDS
-// (global_load_lds_dwordx4: each lane's 16 bytes land at the wavefront's LDS
-// base + 16 x lane, so the row swizzle is applied by choosing which chunk each
-// lane fetches) through a ring of STG stages, STG - 1 steps' loads in flight while
-// one is multiplied, with no registers held for them and no register-to-LDS copy.
-// The waits are explicit (this step's loads counted down, then a bare barrier): a
-// __syncthreads would wait for every load in flight.  Rows past M or N fetch the
-// last row (their outputs are dropped).  Four wavefronts in a 2 x 2 grid, each
-// owning 64 rows x 64 WNT columns: a 128 x 128 WNT block.
+// bf16 weights: a K step's tiles go from global memory straight into LDS (buffer
+// loads to LDS: each lane's 16 bytes land at its wavefront's LDS base + 16 x lane,
+// so the row swizzle is applied by choosing which chunk each lane fetches) through
+// a ring of STG stages, with no registers held for them and no register-to-LDS
+// copy.  The waits are explicit (a step's loads counted down, then a bare barrier): a
+// __syncthreads would wait for every load in flight.  One lane offset serves all
+// loads of an operand: the row ranges differ in their buffer descriptors (scalar
+// registers), whose bounds return zeros for rows past M or N (their outputs are
+// dropped).
 //
-// The loop is bound by LDS traffic, not by the matrix cores: per K step a
-// wavefront reads NT x 4 activation fragments and 4 WNT weight fragments
-// (16 bytes a lane each) for NT x 16 WNT products, and the stage fills write
-// (NT + WNT) x 8 KB per workgroup.  Wider wavefront tiles (WNT = 2) re-read
-// each activation fragment for twice the columns, which cuts the bytes per
-// product by a third or more when the activation has two or three terms.
-// Two stages keep two workgroups per CU (2 x 80 KB at NT = 3, WNT = 2).
-constexpr int kDmaStages = 2;
-
+// Shape: WMW x WNW wavefronts, each 16 TMW x 16 TNW outputs.
+//
+// Schedule: the activation fragments are read GI row tiles at a time, one group
+// ahead of the products that use them, and the next step's weight fragments and
+// first group behind the step's last products: after its last fragment read of a
+// step a wavefront waits for the next stage and the barrier, refills the stage just
+// read, and then multiplies the last group while the next step's fragments arrive.
+// So no product waits for an LDS read issued just before it.  K is walked in pairs
+// of steps (two register sets in turn).
+//
+// The products are formed as W A^T: a lane then holds four consecutive columns of
+// one row and stores 16 bytes (fp32).  For SwiGLU the weight rows of a tile are
+// dealt so that a lane's four tiles are sixteen consecutive columns, i.e. eight
+// outputs, 16 bytes per term plane.
 __device__ __forceinline__ void dma16(const bf16_t* g, bf16_t* lds_wave) {
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds_wave, 16, 0, 0);
 }
@@ -291,15 +296,22 @@ __device__ __forceinline__ void wait_vm_lgkm() {
   __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | (7 << 4));
 }
 
-template <int NT, int EPI, int STG = kDmaStages, int WNT = 1, bool NMAJ = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WNT == 2 ? 2 : 1))) void k_gemm_dma(const bf16_t* __restrict__ A, size_t a_plane,
-                                                  int lda, const bf16_t* __restrict__ W, int M,
-                                                  int N, int K, int ks, float* __restrict__ C,
-                                                  size_t c_split, int ldc, ActBuf H, int ldh) {
-  constexpr int BM = 128, BN = 128 * WNT, FN = 4 * WNT;  // FN: 16-column tiles per wavefront
-  constexpr int TILE = 128 * kLDK;            // bf16 elements of one 128-row tile of a step
-  constexpr int STAGE = (NT + WNT) * TILE;    // NT activation planes, then WNT weight tiles
-  constexpr int PER_LANE = (NT + WNT) * 2;    // 16-byte units per lane per stage
+template <int NT, int EPI, int WMW, int WNW, int TMW, int TNW, int STG, int GI, bool NMAJ>
+__global__ __launch_bounds__(64 * WMW * WNW) __attribute__((amdgpu_waves_per_eu(2))) void
+k_gemm_dma(const bf16_t* __restrict__ A, size_t a_plane, int lda, const bf16_t* __restrict__ W,
+           int M, int N, int K, int ks, float* __restrict__ C, size_t c_split, int ldc, ActBuf H,
+           int ldh) {
+  constexpr int NW = WMW * WNW, BM = 16 * TMW * WMW, BN = 16 * TNW * WNW;
+  constexpr int PAP = BM * 4 / (64 * NW);       // 16-byte units per lane: a plane of A,
+  constexpr int PA = NT * PAP;                  // all of A,
+  constexpr int PB = BN * 4 / (64 * NW);        // and W, per stage
+  constexpr int PER = PA + PB, STAGE = (NT * BM + BN) * kLDK;
+  constexpr int GP = TMW / GI, G = NT * GP;     // groups per plane and step
+  constexpr bool DEAL = EPI == GEMV_SWIGLU;
+  static_assert(BM * 4 % (64 * NW) == 0 && BN * 4 % (64 * NW) == 0, "whole units per lane");
+  static_assert(TMW % GI == 0 && G % 2 == 0, "an even number of groups");
+  static_assert(!DEAL || TNW % 4 == 0, "sixteen consecutive columns per lane");
+  static_assert(STG >= 2 && STG <= 3 && 2 * PER < 64, "stage ring");
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
 
   const int n_mt = (M + BM - 1) / BM, n_nt = (N + BN - 1) / BN;
@@ -323,86 +335,152 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WNT == 2 ? 
   const int kbeg = blockIdx.y * ks;
   C += blockIdx.y * c_split;
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wm = wave >> 1, wn = wave & 1;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wm = wave / WNW, wn = wave % WNW;
 
-  // unit u = (i * 4 + wave) * 64 + lane of a stage holds (128-row tile u / 512,
-  // row (u % 512) / 4, LDS chunk u % 4), i.e. the row's global chunk
-  // (u % 4) ^ lds_swz(row); tiles 0..NT-1 are the activation planes, NT.. the weights
-  const bf16_t* src[PER_LANE];
-#pragma unroll
-  for (int i = 0; i < PER_LANE; ++i) {
-    const int u = (i * 4 + wave) * 64 + lane, mat = u >> 9, r = (u & 511) >> 2;
-    const int c = (u & 3) ^ lds_swz(r);
-    if (mat < NT)
-      src[i] = A + mat * a_plane + (size_t)min(m0 + r, M - 1) * lda + kbeg + c * 8;
-    else
-      src[i] = W + (size_t)min(n0 + (mat - NT) * 128 + r, N - 1) * K + kbeg + c * 8;
-  }
+  // LDS chunk of a weight row: as lds_swz, or for dealt rows (a fragment's sixteen
+  // lanes read rows 16 (l / 4) + l % 4 of 64) by the row's bits 4-5, so that they
+  // cover all 64 banks once either way
+  auto w_swz = [](int row) { return DEAL ? (row >> 4) & 3 : lds_swz(row); };
+  // this lane's unit of a load of 16 NW rows: row r0 of them (4 lanes a row); the
+  // weight rows' swizzle depends on the row range when dealt, the offset with it
+  const int r0 = wave * 16 + (lane >> 2);
+  const int offA = (int)(((size_t)r0 * lda + ((lane & 3) ^ lds_swz(r0)) * 8) * 2);
+  const int offW = (int)(((size_t)r0 * K + ((lane & 3) ^ w_swz(r0)) * 8) * 2);
+  static_assert(!DEAL || (NW * 16) % 64 == 0, "the swizzle is the same in every row range");
   auto issue = [&](int stage, int kt) {
     bf16_t* sb = smem + stage * STAGE;
 #pragma unroll
-    for (int i = 0; i < PER_LANE; ++i) dma16(src[i] + kt * kBK, sb + (i * 4 + wave) * 512);
+    for (int i = 0; i < PER; ++i) {
+      const bool isA = i < PA;
+      const int rr = (isA ? i % PAP : i - PA) * NW * 16;  // first row of the range
+      const int ld = isA ? lda : K, cnt = min((isA ? M - m0 : N - n0) - rr, NW * 16);
+      const bf16_t* base = isA ? A + (i / PAP) * a_plane + (size_t)(m0 + rr) * lda + kbeg
+                               : W + (size_t)(n0 + rr) * K + kbeg;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rsrc(base, cnt > 0 ? ((size_t)(cnt - 1) * ld + ks) * 2 : 0),
+          (__attribute__((address_space(3))) void*)(sb + (i * NW + wave) * 512), 16,
+          isA ? offA : offW, kt * (kBK * 2), 0, 0);
+    }
   };
 
-  floatx4_t acc[4][FN];
+  floatx4_t acc[TMW][TNW];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TMW; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-  const int fr = lane & 15, fk = (lane >> 4) * 8;
-
-  static_assert(STG >= 2 && STG <= 4, "stage ring of 2-4");
-  const int KT = ks / kBK;
+    for (int j = 0; j < TNW; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  const int fr = lane & 15, fc = lane >> 4;
+  // weight row of the wavefront's range that lane fr of tile j multiplies
+  auto w_row = [&](int j) {
+    return wn * 16 * TNW + (DEAL ? (j / 4) * 64 + (fr >> 2) * 16 + (j % 4) * 4 + (fr & 3) : j * 16 + fr);
+  };
+  auto readW = [&](const bf16_t* sb, bf16x8_t (&b)[TNW]) {
 #pragma unroll
-  for (int s = 0; s < STG - 1; ++s)
-    if (s < KT) issue(s, s);
-  for (int kt = 0; kt < KT; ++kt) {
-    // this step's units have landed (the next steps' may still be in flight) and
-    // every wavefront is done reading the stage that is refilled next
-    const int ahead = min(STG - 2, KT - 1 - kt);  // later steps already issued
-    if (ahead >= 2) wait_vm_lgkm<2 * PER_LANE>();
-    else if (ahead == 1) wait_vm_lgkm<PER_LANE>();
+    for (int j = 0; j < TNW; ++j) {
+      const int row = w_row(j);
+      b[j] = *reinterpret_cast<const bf16x8_t*>(sb + (NT * BM + row) * kLDK + 8 * (fc ^ w_swz(row)));
+    }
+  };
+  auto readA = [&](const bf16_t* sb, int g, bf16x8_t (&a)[GI]) {
+#pragma unroll
+    for (int i = 0; i < GI; ++i)
+      a[i] = *reinterpret_cast<const bf16x8_t*>(
+          sb + lds_chunk((g / GP) * BM + wm * 16 * TMW + (g % GP * GI + i) * 16 + fr, fc));
+  };
+  auto mult = [&](int g, const bf16x8_t (&a)[GI], const bf16x8_t (&b)[TNW]) {
+#pragma unroll
+    for (int i = 0; i < GI; ++i)
+#pragma unroll
+      for (int j = 0; j < TNW; ++j) {
+        floatx4_t& c = acc[g % GP * GI + i][j];
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], c, 0, 0, 0);
+      }
+  };
+  // wait for a stage: `later` stages were issued after it
+  auto wait_stage = [&](int later) {
+    if (later >= 2) wait_vm_lgkm<2 * PER>();
+    else if (later == 1) wait_vm_lgkm<PER>();
     else wait_vm_lgkm<0>();
-    __builtin_amdgcn_s_barrier();
-    if (kt + STG - 1 < KT) issue((kt + STG - 1) % STG, kt + STG - 1);
+  };
+  const int KT = ks / kBK;  // even
+#pragma unroll
+  for (int s = 0; s < STG; ++s)
+    if (s < KT) issue(s, s);
+  wait_stage(min(STG, KT) - 1);
+  __builtin_amdgcn_s_barrier();
+  bf16x8_t b0[TNW], b1[TNW], a0[GI], a1[GI];
+  readW(smem, b0);
+  readA(smem, 0, a0);
+  // one K step on the weight fragments b; leaves the next step's in bn (after the
+  // last step: whatever the stage holds, unused)
+  auto step = [&](int kt, const bf16x8_t (&b)[TNW], bf16x8_t (&bn)[TNW]) {
     const bf16_t* sb = smem + (kt % STG) * STAGE;
-    // weight fragments: wavefront column block wn covers weight rows
-    // [64 WNT wn, 64 WNT (wn + 1)) of the block, i.e. of tile (64 WNT wn + 16 j) / 128
-    bf16x8_t bfr[FN];
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int row = wn * 64 * WNT + j * 16 + fr;
-      bfr[j] = *reinterpret_cast<const bf16x8_t*>(sb + (NT + row / 128) * TILE +
-                                                  lds_chunk(row % 128, fk / 8));
+    for (int g = 0; g < G - 1; ++g) {
+      if (g & 1) readA(sb, g + 1, a0);
+      else readA(sb, g + 1, a1);
+      __builtin_amdgcn_sched_barrier(0);  // the reads stay ahead of the products
+      if (g & 1) mult(g, a1, b);
+      else mult(g, a0, b);
+      __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int p = 0; p < NT; ++p) {
-      bf16x8_t af[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        af[i] = *reinterpret_cast<const bf16x8_t*>(sb + p * TILE +
-                                                   lds_chunk(wm * 64 + i * 16 + fr, fk / 8));
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    }
+    wait_stage(min(STG - 2, KT - 2 - kt));
+    __builtin_amdgcn_s_barrier();
+    if (kt + STG < KT) issue(kt % STG, kt + STG);
+    const bf16_t* sn = smem + ((kt + 1) % STG) * STAGE;
+    readW(sn, bn);
+    readA(sn, 0, a0);
+    __builtin_amdgcn_sched_barrier(0);
+    mult(G - 1, a1, b);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int kt = 0; kt < KT; kt += 2) {
+    step(kt, b0, b1);
+    step(kt + 1, b1, b0);
   }
 
+  // lane: row 16 i + fr, columns 4 fc + r of tile j (dealt: 16 fc + 4 (j % 4) + r of
+  // the 64 of four tiles)
+  const bool vec = N % 4 == 0 && ldc % 4 == 0;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < TMW; ++i) {
+    const int m = m0 + wm * 16 * TMW + i * 16 + fr;
+    if (m >= M) continue;
+    if constexpr (DEAL) {
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
+      for (int j = 0; j < TNW; j += 4) {
+        const int n = n0 + wn * 16 * TNW + j * 16 + fc * 16;
+        float o[8];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm * 64 + i * 16 + (lane >> 4) * 4 + r;
-        const int n = n0 + wn * 64 * WNT + j * 16 + (lane & 15);
-        const float v = acc[i][j][r];
-        const float o = EPI == GEMV_SWIGLU ? pair_swap(v) : 0.f;
-        epi_out<EPI>(C, ldc, H, ldh, M, N, m, n, v, o);
+        for (int e = 0; e < 8; ++e) {
+          const floatx4_t& c = acc[i][j + e / 2];
+          o[e] = silu(c[2 * (e & 1)]) * c[2 * (e & 1) + 1];
+        }
+        if (n + 16 <= N && ldh % 8 == 0) {
+          store_act8(H, (size_t)m * ldh + n / 2, o);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (n + 2 * e + 1 < N) store_act(H, (size_t)m * ldh + n / 2 + e, o[e]);
+        }
       }
+    } else {
+#pragma unroll
+      for (int j = 0; j < TNW; ++j) {
+        const int n = n0 + wn * 16 * TNW + j * 16 + fc * 4;
+        float* p = C + (size_t)m * ldc + n;
+        if (vec && n + 4 <= N) {
+          floatx4_t v = acc[i][j];
+          if (EPI == GEMV_RESID) v = *reinterpret_cast<const floatx4_t*>(p) + v;
+          *reinterpret_cast<floatx4_t*>(p) = v;
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (n + r < N) p[r] = EPI == GEMV_RESID ? p[r] + acc[i][j][r] : acc[i][j][r];
+        }
+      }
+    }
+  }
 }
 
 // ------------------------------------------------------------ skinny (M <= 32)
@@ -924,31 +1002,36 @@ static hipError_t gemm_mfma_launch(const ActBuf& A, int lda, const void* W, int 
   return hipGetLastError();
 }
 
-template <int NT, int EPI, int STG = kDmaStages, int WNT = 1, bool NMAJ = false>
+template <int NT, int EPI, int WMW, int WNW, int TMW, int TNW, int STG, int GI, bool NMAJ>
 static hipError_t gemm_dma_launch(const ActBuf& A, int lda, const void* W, int M, int N, int K,
                                   float* C, int ldc, const ActBuf& H, int ldh, hipStream_t st,
                                   int nsplit = 1, size_t c_split = 0) {
-  const int n_mt = (M + 127) / 128, n_nt = (N + 128 * WNT - 1) / (128 * WNT);
+  constexpr int BM = 16 * TMW * WMW, BN = 16 * TNW * WNW;
+  if (K % (2 * kBK * nsplit)) return hipErrorInvalidValue;  // K ranges of whole pairs of steps
+  const int n_mt = (M + BM - 1) / BM, n_nt = (N + BN - 1) / BN;
   const int grid = NMAJ ? 8 * ((n_nt + 7) / 8) * n_mt : (n_mt * n_nt + 7) / 8 * 8;
-  const size_t lds = (size_t)STG * (NT + WNT) * 128 * kLDK * sizeof(bf16_t);
-  auto fn = &k_gemm_dma<NT, EPI, STG, WNT, NMAJ>;
+  const size_t lds = (size_t)STG * (NT * BM + BN) * kLDK * sizeof(bf16_t);
+  auto fn = &k_gemm_dma<NT, EPI, WMW, WNW, TMW, TNW, STG, GI, NMAJ>;
   if (lds > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(fn, dim3(grid, nsplit), dim3(256), lds, st, A.planes, A.plane_stride, lda,
-                     static_cast<const bf16_t*>(W), M, N, K, K / nsplit, C, c_split, ldc, H, ldh);
+  hipLaunchKernelGGL(fn, dim3(grid, nsplit), dim3(64 * WMW * WNW), lds, st, A.planes,
+                     A.plane_stride, lda, static_cast<const bf16_t*>(W), M, N, K, K / nsplit, C,
+                     c_split, ldc, H, ldh);
   return hipGetLastError();
 }
 
-// Block shape 128 x 128 (four waves of 64 x 64).  Measured on the projection
-// shapes of 1B-32B models at 1-2K rows, it beats 256 x 128 blocks by 14-35%: the
-// smaller block keeps two workgroups resident per CU, which hides the global-load
-// latency of the next K slice better than the halved weight re-reads save.
-// bf16 weights from 1024 rows on: 64 x 128 wavefront tiles (128 x 256 blocks),
-// each XCD owning a range of weight column tiles.  Measured with two or three
-// activation terms: 8B gate/up 539 -> 504 us at 1024 rows, 32B gate/up 3202 ->
-// 2050 and QKV 528 -> 426 us at 2048 rows; below 1024 rows the halved block
-// count loses (1B QKV at 512 rows 56 -> 87 us, 128-row chunk tails 1.3-1.6x).
+// Blocks of 128 x 128 (four wavefronts of 64 x 64), and from kWideRows rows on of
+// 128 x 256 (64 x 128 a wavefront: half the activation fragment reads per product),
+// each XCD owning a range of weight column tiles; two workgroups per CU either way.
+// Below 1024 rows the halved block count loses (1B QKV at 512 rows 56 -> 87 us with
+// the wider block).  Two activation terms, random operands, fp32 output: 8B gate/up at
+// 1024 rows 395 us (1218 TFLOP/s), down in four K ranges 205, gate/up at 2048 rows 751
+// (1281); with fragments read just before their products, and 64-bit addresses in
+// vector registers, the same blocks took 425, 228 and 791.  256 x 256 blocks (eight
+// wavefronts, one workgroup per CU, three stages) measured the same (390, 204, 764),
+// 256 x 128 445, 237 and 839, 256 x 256 on four wavefronts of 128 x 128 562, 264 and
+// 1118; raised wavefront priority around the products 1-4% slower.
 constexpr int kWideRows = 1024;
 
 template <int NT, int EPI>
@@ -956,9 +1039,10 @@ static hipError_t gemm_dma_pick(const ActBuf& A, int lda, const void* W, int M, 
                                 float* C, int ldc, const ActBuf& H, int ldh, hipStream_t st,
                                 int nsplit = 1, size_t c_split = 0) {
   if (M >= kWideRows)
-    return gemm_dma_launch<NT, EPI, kDmaStages, 2, true>(A, lda, W, M, N, K, C, ldc, H, ldh, st,
-                                                         nsplit, c_split);
-  return gemm_dma_launch<NT, EPI>(A, lda, W, M, N, K, C, ldc, H, ldh, st, nsplit, c_split);
+    return gemm_dma_launch<NT, EPI, 2, 2, 4, 8, 2, 1, true>(A, lda, W, M, N, K, C, ldc, H, ldh, st,
+                                                            nsplit, c_split);
+  return gemm_dma_launch<NT, EPI, 2, 2, 4, 4, 2, 2, false>(A, lda, W, M, N, K, C, ldc, H, ldh, st,
+                                                           nsplit, c_split);
 }
 
 template <int EPI, bool Q8>
@@ -1060,7 +1144,7 @@ int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split) {
   const int bn = wt == W_BF16 && M >= kWideRows ? 256 : 128;
   const int tiles = ((M + 127) / 128) * ((N + bn - 1) / bn);
   int n = std::max(1, std::min(max_split, 512 / std::max(tiles, 1)));
-  while (n > 1 && (K % (kBK * n) || K / n < 256)) --n;
+  while (n > 1 && (K % (2 * kBK * n) || K / n < 256)) --n;
   return n;
 }
 
@@ -1080,7 +1164,7 @@ static hipError_t gemm_split_nt(int wt, const ActBuf& A, int lda, const void* W,
 
 hipError_t launch_gemm_split(int wt, const ActBuf& A, int lda, const void* W, int M, int N, int K,
                              int nsplit, float* P, size_t p_split, hipStream_t st) {
-  if (nsplit < 1 || K % (kBK * nsplit) || M <= 32 || (wt != W_BF16 && wt != W_Q8))
+  if (nsplit < 1 || K % (2 * kBK * nsplit) || M <= 32 || (wt != W_BF16 && wt != W_Q8))
     return hipErrorInvalidValue;
   switch (A.nt) {
     case 1: return gemm_split_nt<1>(wt, A, lda, W, M, N, K, nsplit, P, p_split, st);

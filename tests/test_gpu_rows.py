@@ -1,6 +1,5 @@
-"""The few-row products (short prompts and batched decode steps) at the edges of
-their row tiles and launch shapes, bf16 and 8-bit weights, against the float64
-oracle: logits, and every cached key and value of every row.
+"""The matrix products of prompts and batched decode steps at the edges of their
+row tiles and launch shapes, bf16 and 8-bit weights, against the float64 oracle: logits, and every cached key and value of every row.
 
 Tolerances: logits 1e-3 of the largest (fp32-accurate activations).  A cached key
 or value that lies next to a rounding boundary may round the other way, one bf16
@@ -64,6 +63,30 @@ def test_short_prompts_match_oracle(cuda_ok, name, weights):
             print(f"[rows] {name} {weights} {n} rows: {inf_rel(lg, ref[n - 1]):.2e}", flush=True)
             assert inf_rel(lg, ref[n - 1]) <= 1e-3, n
             assert tok == int(np.argmax(lg)), n
+            check_kv(m, orc, n)
+    finally:
+        m.close()
+
+
+@pytest.mark.parametrize("weights", ["bf16", "q8"])
+def test_long_prompts_match_oracle(cuda_ok, weights):
+    """129 to 1281 rows: the tiled products with ragged row and column tiles (384, 512
+    and 2304 columns against tiles of 128 and 256), either side of the row count
+    where the wider tile starts."""
+    from paper_2608_24204_amd.binding import WiciModel
+    cfg, w, w64 = setup("narrow", weights)
+    sizes = [200, 257, 500, 640, 1023, 1024, 1281]
+    toks = np.random.default_rng(4).integers(0, cfg.vocab, sizes[-1]).astype(np.int32)
+    orc = DecoderOracle(cfg, w64, max_seq=sizes[-1])
+    ref = orc.full(toks)
+    m = WiciModel(cfg, max_seq=sizes[-1])
+    try:
+        m.load_weights(w)
+        for n in sizes:
+            m.reset_kv()
+            tok, lg = m.prefill(toks[:n], want_logits=True)
+            print(f"[rows] {weights} {n} rows: {inf_rel(lg, ref[n - 1]):.2e}", flush=True)
+            assert inf_rel(lg, ref[n - 1]) <= 1e-3, n
             check_kv(m, orc, n)
     finally:
         m.close()
