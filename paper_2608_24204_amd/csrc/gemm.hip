@@ -627,7 +627,7 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(const bf16_t* __restrict__ 
 constexpr int kRowsKC = 128;       // K ranges are multiples of this (whole slices)
 constexpr int kRowsSyncLine = 64;  // ints per tile: counter at 0, XCD records from 32
 constexpr int kRowsMaxTiles = kGemmRowsSyncInts / kRowsSyncLine;  // tiles that can be split
-// Rows the kernel takes: while it beats the 128-row tiles of the prefill products.
+// Rows the kernel takes.
 constexpr int kRowsMaxBf16 = 128, kRowsMaxQ8 = 64;
 
 // LDS chunk (16 bytes) of a row's chunk c, for rows of CH chunks: rows of 256 bytes
@@ -1021,28 +1021,75 @@ static hipError_t gemm_dma_launch(const ActBuf& A, int lda, const void* W, int M
   return hipGetLastError();
 }
 
-// Blocks of 128 x 128 (four wavefronts of 64 x 64), and from kWideRows rows on of
-// 128 x 256 (64 x 128 a wavefront: half the activation fragment reads per product),
-// each XCD owning a range of weight column tiles; two workgroups per CU either way.
-// Below 1024 rows the halved block count loses (1B QKV at 512 rows 56 -> 87 us with
-// the wider block).  Two activation terms, random operands, fp32 output: 8B gate/up at
-// 1024 rows 395 us (1218 TFLOP/s), down in four K ranges 205, gate/up at 2048 rows 751
+// Tiles of the bf16 product (four wavefronts each): 128 x 256 (64 x 128 a wavefront:
+// half the activation fragment reads per product), 128 x 128, and 64 x 128 (64 x 32 a
+// wavefront, three stages, three workgroups per CU, for few rows).
+//   Two activation terms, random operands, fp32 output, 128 x 256: 8B gate/up at 1024
+// rows 395 us (1218 TFLOP/s), down in four K ranges 205, gate/up at 2048 rows 751
 // (1281); with fragments read just before their products, and 64-bit addresses in
 // vector registers, the same blocks took 425, 228 and 791.  256 x 256 blocks (eight
 // wavefronts, one workgroup per CU, three stages) measured the same (390, 204, 764),
 // 256 x 128 445, 237 and 839, 256 x 256 on four wavefronts of 128 x 128 562, 264 and
 // 1118; raised wavefront priority around the products 1-4% slower.
-constexpr int kWideRows = 1024;
+enum TileShape { TILE_128x256 = 0, TILE_128x128 = 1, TILE_64x128 = 2 };
+
+// Time of a product of M x N x K in nsplit K ranges on a tile shape, in us: rounds of
+// resident workgroups times K steps, a step's time depending on how many workgroups
+// share a CU (a lone one waits out its loads; a second and third fill in until the
+// matrix cores are busy) and on the activation terms; plus the partials written and
+// read.  The step times are fitted to 340 measured products of 1B, 8B and 32B shapes
+// at 128 to 2048 rows (7% rms).
+static float tile_time(int shape, int nt, int M, int N, int K, int nsplit) {
+  static const struct { int bm, bn, occ; float t[3][2]; } P[3] = {
+      {128, 256, 2, {{.59f, .18f}, {.36f, .67f}, {0.f, 0.f}}},
+      {128, 128, 2, {{.36f, .13f}, {.34f, .33f}, {0.f, 0.f}}},
+      {64, 128, 3, {{.26f, .05f}, {.49f, .10f}, {.24f, .36f}}}};
+  const auto& p = P[shape];
+  auto step = [&](int k) { return p.t[k - 1][0] + p.t[k - 1][1] * (float)nt; };
+  const long n = (long)((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn) * nsplit;
+  const long rounds = n / (256 * p.occ), rest = n % (256 * p.occ);
+  const float steps = (float)K / (kBK * nsplit);
+  float us = 3.3f + steps * (float)rounds * step(p.occ);
+  if (rest) {
+    const int k = (int)((rest + 255) / 256);
+    const float lo = step(k > 1 ? k - 1 : 1), f = (float)(rest - 256 * (k - 1)) / 256.f;
+    us += steps * (lo + (step(k) - lo) * (0.5f + 0.5f * f));
+  }
+  if (nsplit > 1) us += (float)nsplit * M * N * 1.2e-6f;
+  return us;
+}
+
+// The fastest tile for a split count.  By measurement (us, 128 x 128 against 128 x 256):
+// 8B gate/up 120 and 127 at 200 rows, 191 and 177 at 333, 255 and 203 at 512, 366
+// and 295 at 700; O in four ranges 44 and 46 at 512; 64 x 128 takes 17 for O in four
+// ranges at 128 rows against 26 and 36.
+static int tile_shape(int nt, int M, int N, int K, int nsplit) {
+  int best = 0;
+  for (int s = 1; s < 3; ++s)
+    if (tile_time(s, nt, M, N, K, nsplit) < tile_time(best, nt, M, N, K, nsplit)) best = s;
+  return best;
+}
 
 template <int NT, int EPI>
 static hipError_t gemm_dma_pick(const ActBuf& A, int lda, const void* W, int M, int N, int K,
                                 float* C, int ldc, const ActBuf& H, int ldh, hipStream_t st,
                                 int nsplit = 1, size_t c_split = 0) {
-  if (M >= kWideRows)
-    return gemm_dma_launch<NT, EPI, 2, 2, 4, 8, 2, 1, true>(A, lda, W, M, N, K, C, ldc, H, ldh, st,
-                                                            nsplit, c_split);
-  return gemm_dma_launch<NT, EPI, 2, 2, 4, 4, 2, 2, false>(A, lda, W, M, N, K, C, ldc, H, ldh, st,
-                                                           nsplit, c_split);
+  switch (tile_shape(NT, M, N, K, nsplit)) {
+    case TILE_128x256:
+      return gemm_dma_launch<NT, EPI, 2, 2, 4, 8, 2, 1, true>(A, lda, W, M, N, K, C, ldc, H, ldh,
+                                                              st, nsplit, c_split);
+    case TILE_128x128:
+      return gemm_dma_launch<NT, EPI, 2, 2, 4, 4, 2, 2, false>(A, lda, W, M, N, K, C, ldc, H, ldh,
+                                                               st, nsplit, c_split);
+    default:
+      // (SwiGLU's dealt columns need four tiles a wavefront: two wavefronts of 64 x 64)
+      if constexpr (EPI == GEMV_SWIGLU)
+        return gemm_dma_launch<NT, EPI, 2, 2, 2, 4, 3, NT % 2 ? 1 : 2, true>(
+            A, lda, W, M, N, K, C, ldc, H, ldh, st, nsplit, c_split);
+      else
+        return gemm_dma_launch<NT, EPI, 1, 4, 4, 2, 3, 2, true>(A, lda, W, M, N, K, C, ldc, H, ldh,
+                                                                st, nsplit, c_split);
+  }
 }
 
 template <int EPI, bool Q8>
@@ -1137,15 +1184,24 @@ static hipError_t gemm_f32(const ActBuf& A, int lda, const WT* W, int M, int N, 
 }
 
 // Split K for products with too few output tiles to fill the chip: as many
-// splits as still leave at most two blocks per CU (512), each at least 256 deep.
-// (Blocks of 128 x 256 for bf16 weights from kWideRows rows on, else 128 x 128.)
+// splits (at most four) as still leave at most two blocks per CU (512), each at least
+// 256 deep.  bf16 weights: or another count, up to eight, that tile_time puts at
+// least 12% below that (8B down at 700 rows 199 us in two ranges, 172 in eight; 32B
+// down at 2048 rows, whose 320 tiles leave 512 places unevenly filled, 1267 us whole
+// and 1037 in four ranges).
 int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split) {
   if (nt < 1 || M <= 32 || (wt != W_BF16 && wt != W_Q8)) return 1;
-  const int bn = wt == W_BF16 && M >= kWideRows ? 256 : 128;
+  auto fits = [&](int n) { return K % (2 * kBK * n) == 0 && K / n >= 256; };
+  const int bn = wt == W_BF16 && M >= 1024 ? 256 : 128;
   const int tiles = ((M + 127) / 128) * ((N + bn - 1) / bn);
-  int n = std::max(1, std::min(max_split, 512 / std::max(tiles, 1)));
-  while (n > 1 && (K % (2 * kBK * n) || K / n < 256)) --n;
-  return n;
+  int n = std::max(1, std::min({max_split, 4, 512 / std::max(tiles, 1)}));
+  while (n > 1 && !fits(n)) --n;
+  if (wt == W_Q8) return n;
+  auto time = [&](int s) { return tile_time(tile_shape(nt, M, N, K, s), nt, M, N, K, s); };
+  int best = n;
+  for (int s = 1; s <= std::min(max_split, 8); ++s)
+    if ((s == 1 || fits(s)) && time(s) < time(best)) best = s;
+  return time(best) < 0.88f * time(n) ? best : n;
 }
 
 template <int NT>
@@ -1155,10 +1211,6 @@ static hipError_t gemm_split_nt(int wt, const ActBuf& A, int lda, const void* W,
   if (wt == W_Q8)
     return gemm_mfma_launch<NT, 2, 2, GEMV_STORE, true>(A, lda, W, M, N, K, P, N, none, 0, st,
                                                          nsplit, p_split);
-  // the residual products (O, down: few output columns, split K) from 1024 rows
-  // on: 8B down 274 -> 235 us, O 70 -> 66 us (the wider tile halves the
-  // activation fragment reads per product; the placement lets the row tiles of
-  // one weight tile share it in the XCD's L2)
   return gemm_dma_pick<NT, GEMV_STORE>(A, lda, W, M, N, K, P, N, none, 0, st, nsplit, p_split);
 }
 
@@ -1232,6 +1284,14 @@ static hipError_t gemm_rows(const ActBuf& A, int lda, const void* W, int M, int 
     if (M <= 96) return go(RowsShape<6, 2, 64, 3>{});
     return go(RowsShape<8, 2, 64, 2>{});
   }
+}
+
+// Measured against the tiled product in K ranges whose partials a row norm adds
+// anyway (us, two terms): O 20 against 17 at 64 rows and 30 against 17 at 96, down 43
+// against 50 and 54 against 50; but 8B gate/up 78 against 97 at 96 rows, 95 against 97
+// at 128.
+bool gemm_rows_best(int wt, int nt, int M, int N, int K) {
+  return gemm_rows_takes(wt, nt, M, K) && (M <= 64 || N >= 192 * 128);
 }
 
 bool gemm_rows_takes(int wt, int nt, int M, int K) {

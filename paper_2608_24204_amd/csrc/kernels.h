@@ -199,12 +199,12 @@ bool attn_group_supported(int G);
 // fp32) or SWIGLU (H[M, N/2] (ldh) = silu(gate) * up of the packed column pairs,
 // written as an activation buffer).  A.nt == 0: vector fp32 product (W bf16 or
 // fp32); A.nt = 1..3: matrix-core product of the nt bf16 planes with bf16 W.
-// K must be a multiple of 32.
+// K must be a multiple of 32 (64 for bf16 W and more than 32 rows).
 hipError_t launch_gemm(int wt, int epi, const ActBuf& A, int lda, const void* W, int M,
                        int N, int K, float* C, int ldc, const ActBuf& H, int ldh,
                        hipStream_t st);
 // The same product (matrix cores, nt >= 1, M > 32) over nsplit K ranges of equal
-// depth (K a multiple of 32 nsplit): range s writes P + s * p_split ([M, N], row
+// depth (K a multiple of 64 nsplit): range s writes P + s * p_split ([M, N], row
 // stride N, fp32).  gemm_split_count picks nsplit (1: do not split).
 hipError_t launch_gemm_split(int wt, const ActBuf& A, int lda, const void* W, int M, int N, int K,
                              int nsplit, float* P, size_t p_split, hipStream_t st);
@@ -220,6 +220,8 @@ int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split);
 // the error path).  Launches that share sync must not overlap.
 constexpr int kGemmRowsSyncInts = 512 * 64;
 bool gemm_rows_takes(int wt, int nt, int M, int K);
+// Whether that beats the tiled product split along K (launch_gemm_split).
+bool gemm_rows_best(int wt, int nt, int M, int N, int K);
 hipError_t launch_gemm_rows(int wt, int epi, const ActBuf& A, int lda, const void* W, int M,
                             int N, int K, float* C, int ldc, const ActBuf& H, int ldh,
                             float* part, size_t part_floats, int* sync, int* fault,

@@ -277,11 +277,15 @@ static bool resid_sum_reg(float* x, const float* P, size_t p_split, const float*
                           int T, int d, const ActBuf& y, hipStream_t st) {
   if (d % 1024 || p_split % 4) return false;
   switch (d / 1024) {
-#define WICI_RS(NV)                                                                           \
-  case NV:                                                                                    \
-    hipLaunchKernelGGL((k_resid_sum_rmsnorm_reg<NS, NV>), dim3(T), dim3(256), 0, st, x, P, \
-                       p_split, gain, eps, d, y);                                             \
-    return true;
+// (partials of up to 40 values of four per thread stay in registers)
+#define WICI_RS(NV)                                                                               \
+  case NV:                                                                                        \
+    if constexpr (NS * NV <= 40) {                                                                \
+      hipLaunchKernelGGL((k_resid_sum_rmsnorm_reg<NS, NV>), dim3(T), dim3(256), 0, st, x, P,      \
+                         p_split, gain, eps, d, y);                                               \
+      return true;                                                                                \
+    }                                                                                             \
+    return false;
     WICI_RS(1) WICI_RS(2) WICI_RS(3) WICI_RS(4) WICI_RS(5) WICI_RS(6) WICI_RS(7) WICI_RS(8)
 #undef WICI_RS
     default: return false;
@@ -295,6 +299,10 @@ hipError_t launch_resid_sum_rmsnorm(float* x, const float* P, int nsplit, size_t
   const bool reg = nsplit == 2   ? resid_sum_reg<2>(x, P, p_split, gain, eps, T, d, y, st)
                    : nsplit == 3 ? resid_sum_reg<3>(x, P, p_split, gain, eps, T, d, y, st)
                    : nsplit == 4 ? resid_sum_reg<4>(x, P, p_split, gain, eps, T, d, y, st)
+                   : nsplit == 5 ? resid_sum_reg<5>(x, P, p_split, gain, eps, T, d, y, st)
+                   : nsplit == 6 ? resid_sum_reg<6>(x, P, p_split, gain, eps, T, d, y, st)
+                   : nsplit == 7 ? resid_sum_reg<7>(x, P, p_split, gain, eps, T, d, y, st)
+                   : nsplit == 8 ? resid_sum_reg<8>(x, P, p_split, gain, eps, T, d, y, st)
                                  : false;
   if (!reg)
     hipLaunchKernelGGL(k_resid_sum_rmsnorm, dim3(T), dim3(256), 0, st, x, P, nsplit, p_split,

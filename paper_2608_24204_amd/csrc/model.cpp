@@ -30,7 +30,10 @@ constexpr size_t kAlign = 256;
 constexpr int kMaxGemvBlocks = 1024;
 constexpr int kMaxBatch = 256;  // sequences per batched decode step
 constexpr size_t kFuseRopeMaxBlocks = 3 * 4 * 256;  // see enqueue_decode_batch
-constexpr int kMaxKSplit = 4;   // K ranges of a prefill residual product (partials kept)
+constexpr int kMaxKSplit = 4;   // K ranges of a prefill residual product of whole chunks
+                                // (partials kept; more ranges for fewer rows)
+constexpr int kMaxRowSplit = 8; // partials the row norms add, and the RoPE + append
+constexpr int kMaxRopeSplit = 4;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 size_t dsize(int32_t dt) { return dt == WICI_BF16 ? 2 : 4; }
@@ -408,29 +411,33 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
   // they are split along K into partials that the next row RMSNorm adds to x
   // (in split order, so the result does not depend on scheduling).
   float* P = m->S<float>(L.kpart);
-  const size_t p_split = C * d;
+  const size_t p_split = (size_t)T * d;
+  // partials of T rows of width n that fit the split buffer
+  auto room = [&](int n, int most) {
+    return (int)std::min<size_t>(most, kMaxKSplit * C * d / ((size_t)T * n));
+  };
   // Few rows: the weight-streaming products, which add their K ranges in the launch
   // (P holds the partials; a misplaced range is reported through the state).
   int* gsync = m->S<int>(L.gemm_sync);
   int* gfault = &reinterpret_cast<DecodeState*>(m->ds + L.state)->fault;
   auto prod = [&](int epi, const wici::ActBuf& in, int K, size_t w, int N, float* out, int ldo,
                   const wici::ActBuf& hout, int ldh) {
-    return wici::gemm_rows_takes(wb, in.nt, T, K)
+    return wici::gemm_rows_best(wb, in.nt, T, N, K)
                ? wici::launch_gemm_rows(wb, epi, in, K, m->dw + w, T, N, K, out, ldo, hout, ldh, P,
                                         (size_t)kMaxKSplit * C * d, gsync, gfault, s)
                : wici::launch_gemm(wb, epi, in, K, m->dw + w, T, N, K, out, ldo, hout, ldh, s);
   };
   auto splits = [&](int terms, int N, int K, int most) {
-    return wici::gemm_rows_takes(wb, terms, T, K)
-               ? 1 : wici::gemm_split_count(wb, terms, T, N, K, most);
+    return wici::gemm_rows_best(wb, terms, T, N, K)
+               ? 1 : wici::gemm_split_count(wb, terms, T, N, K, room(N, most));
   };
-  const int s_o = splits(rd(att, pl.o).nt, d, qd, kMaxKSplit);
-  const int s_d = splits(rd(h, pl.down).nt, d, F, kMaxKSplit);
+  const int s_o = splits(rd(att, pl.o).nt, d, qd, kMaxRowSplit);
+  const int s_d = splits(rd(h, pl.down).nt, d, F, kMaxRowSplit);
   // the QKV projection too, as far as its partials fit the split buffer; they are
   // added (in range order) by the RoPE + append kernel.  Measured at 1024 rows
   // (8B): 185 -> 164 us; at 512 rows (1B): 56 -> 33 us.
-  const int s_q = splits(rd(a, pl.qkv).nt, nqkv, d, std::min(kMaxKSplit, kMaxKSplit * d / nqkv));
-  const size_t q_split = C * nqkv;
+  const int s_q = splits(rd(a, pl.qkv).nt, nqkv, d, kMaxRopeSplit);
+  const size_t q_split = (size_t)T * nqkv;
   int pending = 0;  // splits of the previous down product not yet added to x
   // (the normalised rows are written with as many terms as their product reads)
   auto norm = [&](const float* gain, int nsplit, int terms) {
@@ -536,12 +543,30 @@ hipError_t enqueue_decode_batch(wici_model* m, int B) {
   do {                 \
     if ((e = (call))) return e; \
   } while (0)
+  // the residual products: from the row count where that is faster, tiled in K ranges
+  // whose partials the next row norm adds (as in a prefill chunk)
+  const size_t p_split = (size_t)B * d;
+  auto splits = [&](const wici::ActBuf& in, int K) {
+    return wici::gemm_rows_best(wb, in.nt, B, d, K)
+               ? 1 : wici::gemm_split_count(wb, in.nt, B, d, K,
+                                            (int)std::min<size_t>(kMaxRowSplit, kMaxKSplit * C / B));
+  };
+  const int s_o = splits(rd(att, pl.o), qd), s_d = splits(rd(h, pl.down), F);
+  auto resid = [&](const wici::ActBuf& in, int K, size_t w, int nsplit) {
+    return nsplit > 1
+               ? wici::launch_gemm_split(wb, in, K, m->dw + w, B, d, K, nsplit, gpart, p_split, s)
+               : prod(wici::GEMV_RESID, in, K, w, d, x, d, none, 0);
+  };
+  auto norm = [&](const float* gain, int nsplit) {
+    return nsplit > 1 ? wici::launch_resid_sum_rmsnorm(x, gpart, nsplit, p_split, gain, c.rms_eps,
+                                                       B, d, a, s)
+                      : wici::launch_rmsnorm_rows(x, gain, c.rms_eps, B, d, a, s);
+  };
   WICI_TRY(wici::launch_gather_tokens(seqs, B, m->S<int32_t>(L.tokens), s));
   WICI_TRY(wici::launch_embed(wb, m->dw + L.embed, c.vocab, d, m->S<int32_t>(L.tokens), B,
                               nullptr, x, s));
   for (int l = 0; l < c.n_layers; ++l) {
-    WICI_TRY(wici::launch_rmsnorm_rows(x, m->W<float>(m->layer(l, L.l_anorm)), c.rms_eps, B, d,
-                                       a, s));
+    WICI_TRY(norm(m->W<float>(m->layer(l, L.l_anorm)), l ? s_d : 1));
     WICI_TRY(prod(wici::GEMV_STORE, rd(a, pl.qkv), d, m->layer(l, L.l_wqkv), nqkv, qkv, nqkv,
                   none, 0));
     if (!fuse_rope)
@@ -549,14 +574,13 @@ hipError_t enqueue_decode_batch(wici_model* m, int B) {
                                               m->W<float>(L.rope_sin), seqs, l, kv, q_scale, s));
     WICI_TRY(wici::launch_attn_decode_batch(kb, qkv, nqkv, B, c.n_heads, kv, seqs, l, L.nsplit,
                                             part_o, part_ml, att, s, fuse_rope ? &rope : nullptr));
-    WICI_TRY(prod(wici::GEMV_RESID, rd(att, pl.o), qd, m->layer(l, L.l_wo), d, x, d, none, 0));
-    WICI_TRY(wici::launch_rmsnorm_rows(x, m->W<float>(m->layer(l, L.l_fnorm)), c.rms_eps, B, d,
-                                       a, s));
+    WICI_TRY(resid(rd(att, pl.o), qd, m->layer(l, L.l_wo), s_o));
+    WICI_TRY(norm(m->W<float>(m->layer(l, L.l_fnorm)), s_o));
     WICI_TRY(prod(wici::GEMV_SWIGLU, rd(a, pl.gu), d, m->layer(l, L.l_wgu), 2 * F, nullptr, 0, h,
                   F));
-    WICI_TRY(prod(wici::GEMV_RESID, rd(h, pl.down), F, m->layer(l, L.l_wdown), d, x, d, none, 0));
+    WICI_TRY(resid(rd(h, pl.down), F, m->layer(l, L.l_wdown), s_d));
   }
-  WICI_TRY(wici::launch_rmsnorm_rows(x, m->W<float>(L.final_norm), c.rms_eps, B, d, a, s));
+  WICI_TRY(norm(m->W<float>(L.final_norm), s_d));
   WICI_TRY(prod(wici::GEMV_STORE, a, d, L.lm_head, c.vocab, logits, c.vocab, none, 0));
   WICI_TRY(wici::launch_argmax_rows(logits, B, c.vocab, seqs, s));
 #undef WICI_TRY

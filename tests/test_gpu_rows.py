@@ -69,13 +69,14 @@ def test_short_prompts_match_oracle(cuda_ok, name, weights):
 
 
 @pytest.mark.parametrize("weights", ["bf16", "q8"])
-def test_long_prompts_match_oracle(cuda_ok, weights):
-    """129 to 1281 rows: the tiled products with ragged row and column tiles (384, 512
-    and 2304 columns against tiles of 128 and 256), either side of the row count
-    where the wider tile starts."""
+@pytest.mark.parametrize("name,sizes", [("narrow", [200, 257, 500, 640, 1023, 1024, 1281]),
+                                        ("wide", [130, 200, 257, 400])])
+def test_long_prompts_match_oracle(cuda_ok, name, sizes, weights):
+    """130 to 1281 rows: the tiled products with ragged row and column tiles (384, 512
+    and 2304 columns against tiles of 128 and 256; 24832 for the wide ones), split
+    along K and not, on every tile shape."""
     from paper_2608_24204_amd.binding import WiciModel
-    cfg, w, w64 = setup("narrow", weights)
-    sizes = [200, 257, 500, 640, 1023, 1024, 1281]
+    cfg, w, w64 = setup(name, weights)
     toks = np.random.default_rng(4).integers(0, cfg.vocab, sizes[-1]).astype(np.int32)
     orc = DecoderOracle(cfg, w64, max_seq=sizes[-1])
     ref = orc.full(toks)
@@ -85,7 +86,7 @@ def test_long_prompts_match_oracle(cuda_ok, weights):
         for n in sizes:
             m.reset_kv()
             tok, lg = m.prefill(toks[:n], want_logits=True)
-            print(f"[rows] {weights} {n} rows: {inf_rel(lg, ref[n - 1]):.2e}", flush=True)
+            print(f"[rows] {name} {weights} {n} rows: {inf_rel(lg, ref[n - 1]):.2e}", flush=True)
             assert inf_rel(lg, ref[n - 1]) <= 1e-3, n
             check_kv(m, orc, n)
     finally:
