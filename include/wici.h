@@ -28,7 +28,8 @@
  *    owns only host state, captured decode graphs (the per-token step, and the
  *    batched step per batch size it led) and a 16-byte pinned, device-mapped
  *    host buffer into which each step's last kernel writes the step state (read
- *    by the host after the stream drains), all released by wici_destroy.
+ *    by the host after the stream drains), and, once it has led a batched step, 18 KB
+ *    of the same for that step's descriptors and states, all released by wici_destroy.
  */
 #ifndef WICI_H
 #define WICI_H
@@ -231,7 +232,8 @@ wici_status wici_bind_memory_shared(wici_model* m, const wici_model* src, void* 
  * token; logits (host, n * vocab, may be NULL) each sequence's fp32 logits,
  * row b for sequence b.  Runs on models[0]'s stream and scratch (n <= its prefill_chunk and
  * <= 256); n == 1 runs models[0]'s own decode step (wici_decode_step), whose
- * weight-streaming products are faster for a single row.  Synchronous.  Errors: WICI_E_ARG (bad pointers or counts, models
+ * weight-streaming products are faster for a single row.  Synchronous, as wici_prefill
+ * is.  Errors: WICI_E_ARG (bad pointers or counts, models
  * that do not share weights and configuration, duplicates, a token id >= vocab,
  * n beyond the scratch), WICI_E_STATE (a model not ready, not prefilled or
  * without a token to feed), WICI_E_CAPACITY (a model at max_seq),

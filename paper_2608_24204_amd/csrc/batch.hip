@@ -9,15 +9,38 @@
 
 namespace wici {
 
-// tokens[b] = sequence b's input token (its state's token)
-__global__ void k_gather_tokens(const SeqDesc* __restrict__ seqs, int B,
-                                int32_t* __restrict__ tokens) {
+// Bound by one read of host memory and one of the states.  One launch in place of a
+// copy of the descriptors and a token launch per sequence (48 sequences: 49 launches and
+// copies of 1.8 us and more a step).
+__global__ void k_batch_begin(const SeqDesc* __restrict__ host_seqs, SeqDesc* __restrict__ seqs,
+                              int B, int32_t* __restrict__ tokens) {
   const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < B) tokens[b] = static_cast<const DecodeState*>(seqs[b].state)->token;
+  if (b >= B) return;
+  // read past every cache: the host rewrites the descriptors between steps
+  static_assert(sizeof(SeqDesc) % 8 == 0, "whole words");
+  constexpr int WORDS = sizeof(SeqDesc) / 8;
+  struct Words { uint64_t w[WORDS]; } v;
+  const uint64_t* src = reinterpret_cast<const uint64_t*>(host_seqs + b);
+#pragma unroll
+  for (int i = 0; i < WORDS; ++i)
+    v.w[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  const SeqDesc sd = __builtin_bit_cast(SeqDesc, v);
+  seqs[b] = sd;
+  DecodeState* st = static_cast<DecodeState*>(sd.state);
+  int token = sd.token;
+  if (token >= 0) {
+    st->token = token;
+    st->bad = 0;
+  } else {
+    token = st->token;
+  }
+  tokens[b] = token;
 }
 
-hipError_t launch_gather_tokens(const SeqDesc* seqs, int B, int32_t* tokens, hipStream_t st) {
-  hipLaunchKernelGGL(k_gather_tokens, dim3((B + 63) / 64), dim3(64), 0, st, seqs, B, tokens);
+hipError_t launch_batch_begin(const SeqDesc* host_seqs, SeqDesc* seqs, int B, int32_t* tokens,
+                              hipStream_t st) {
+  hipLaunchKernelGGL(k_batch_begin, dim3((B + 63) / 64), dim3(64), 0, st, host_seqs, seqs, B,
+                     tokens);
   return hipGetLastError();
 }
 
@@ -159,7 +182,8 @@ hipError_t launch_rope_append_batch(bool kv_bf16, float* qkv, int B, int Hq, con
 // a non-finite logit marks the row failed), then sequence b's state advances:
 // token, position + 1, and the token recorded in its history.
 __global__ __launch_bounds__(1024) void k_argmax_rows(const float* __restrict__ logits, int V,
-                                                     const SeqDesc* __restrict__ seqs) {
+                                                     const SeqDesc* __restrict__ seqs,
+                                                     DecodeState* mirror) {
   __shared__ float sv[16];
   __shared__ int si[16];
   __shared__ int sbad[16];
@@ -205,12 +229,21 @@ __global__ __launch_bounds__(1024) void k_argmax_rows(const float* __restrict__ 
     st->token = tok;
     st->pos = pos;
     seqs[b].hist[pos - 1] = tok;
+    // pinned host copy; `done` last, after a system-scope fence
+    DecodeState* m = mirror + b;
+    m->bad = bad;
+    m->token = tok;
+    m->pos = pos;
+    m->fault = st->fault;
+    __threadfence_system();
+    m->done = 1;
   }
 }
 
 hipError_t launch_argmax_rows(const float* logits, int B, int V, const SeqDesc* seqs,
-                              hipStream_t st) {
-  hipLaunchKernelGGL(k_argmax_rows, dim3(B), dim3(1024), 0, st, logits, V, seqs);
+                              void* host_mirror, hipStream_t st) {
+  hipLaunchKernelGGL(k_argmax_rows, dim3(B), dim3(1024), 0, st, logits, V, seqs,
+                     static_cast<DecodeState*>(host_mirror));
   return hipGetLastError();
 }
 

@@ -133,19 +133,26 @@ struct SeqDesc {
   const int32_t* table;      // its page table
   void* state;               // its DecodeState
   int32_t* hist;             // its token history [max_seq]
+  int32_t token;             // >= 0: the step's input token (a host-given token restarts a
+                             // failed sequence); < 0: the state's
+  int32_t pad;
 };
 
 // Batched decode helpers (row b = sequence b).
-hipError_t launch_gather_tokens(const SeqDesc* seqs, int B, int32_t* tokens, hipStream_t st);
+// The step's first launch: copies the B descriptors from pinned host memory (as the
+// device addresses it) to seqs, sets the given tokens, and gathers every input token.
+hipError_t launch_batch_begin(const SeqDesc* host_seqs, SeqDesc* seqs, int B, int32_t* tokens,
+                              hipStream_t st);
 // Rotate row b's queries in place (times q_scale) and keys at sequence b's position,
 // append keys and values to its cache (layer `layer`; kv gives page, heads, hd).
 hipError_t launch_rope_append_batch(bool kv_bf16, float* qkv, int B, int Hq, const float* cos_t,
                                     const float* sin_t, const SeqDesc* seqs, int layer,
                                     KvLayout kv, float q_scale, hipStream_t st);
 // Greedy token per row of logits [B, V]; advances each sequence's state and history
-// (a row with a non-finite logit gets token -1 and the failed flag).
+// (a row with a non-finite logit gets token -1 and the failed flag).  Row b's new state
+// is also written to host_mirror[b] (pinned host memory), its `done` last.
 hipError_t launch_argmax_rows(const float* logits, int B, int V, const SeqDesc* seqs,
-                              hipStream_t st);
+                              void* host_mirror, hipStream_t st);
 // RoPE tables and the query scale, for a decode attention that applies RoPE and
 // appends the new key and value itself.
 struct RopeIn {

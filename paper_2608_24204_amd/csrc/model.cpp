@@ -219,6 +219,13 @@ struct wici_model {
   // sequences' descriptors are read from device memory, so a graph serves any
   // group of that size)
   std::unordered_map<int, std::pair<hipGraph_t, hipGraphExec_t>> batch_graphs;
+  // pinned, device-mapped memory of the batched steps led by this model (made by the
+  // first): the descriptors a step reads and the states it leaves, kMaxBatch of each,
+  // as the host and as the kernels address them
+  wici::SeqDesc* h_seqs = nullptr;
+  wici::SeqDesc* d_host_seqs = nullptr;
+  DecodeState* h_batch = nullptr;
+  DecodeState* d_batch_mirror = nullptr;
   int gemv_lm_blocks = 0;
 
   bool ready() const { return bound && n_loaded == (int)specs.size(); }
@@ -481,7 +488,7 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
 }
 
 // Enqueue one batched decode step of B sequences (descriptors already in the
-// lead model's scratch) on the lead's stream, in its scratch: row b of every
+// lead model's pinned memory) on the lead's stream, in its scratch: row b of every
 // activation matrix is sequence b.  The projections are the prefill products
 // (matrix cores with the lead's prefill mode, or the vector product), the
 // per-sequence parts (RoPE and append, attention, argmax) read the descriptors.
@@ -509,7 +516,7 @@ hipError_t enqueue_decode_batch(wici_model* m, int B) {
   };
   const wici::ActBuf a = act(L.a, d), att = act(L.att, qd), h = act(L.h, F);
   const wici::ActBuf none{};
-  const wici::SeqDesc* seqs = m->S<wici::SeqDesc>(L.seqs);
+  wici::SeqDesc* seqs = m->S<wici::SeqDesc>(L.seqs);
   float* x = m->S<float>(L.x);
   float* qkv = m->S<float>(L.qkv);
   // attention partials and the logits live in the FFN buffer, free at those times
@@ -562,7 +569,7 @@ hipError_t enqueue_decode_batch(wici_model* m, int B) {
                                                        B, d, a, s)
                       : wici::launch_rmsnorm_rows(x, gain, c.rms_eps, B, d, a, s);
   };
-  WICI_TRY(wici::launch_gather_tokens(seqs, B, m->S<int32_t>(L.tokens), s));
+  WICI_TRY(wici::launch_batch_begin(m->d_host_seqs, seqs, B, m->S<int32_t>(L.tokens), s));
   WICI_TRY(wici::launch_embed(wb, m->dw + L.embed, c.vocab, d, m->S<int32_t>(L.tokens), B,
                               nullptr, x, s));
   for (int l = 0; l < c.n_layers; ++l) {
@@ -582,7 +589,7 @@ hipError_t enqueue_decode_batch(wici_model* m, int B) {
   }
   WICI_TRY(norm(m->W<float>(L.final_norm), s_d));
   WICI_TRY(prod(wici::GEMV_STORE, a, d, L.lm_head, c.vocab, logits, c.vocab, none, 0));
-  WICI_TRY(wici::launch_argmax_rows(logits, B, c.vocab, seqs, s));
+  WICI_TRY(wici::launch_argmax_rows(logits, B, c.vocab, seqs, m->d_batch_mirror, s));
 #undef WICI_TRY
   return hipSuccess;
 }
@@ -609,6 +616,27 @@ hipError_t alloc_state_mirror(wici_model* m) {
   return hipHostGetDevicePointer((void**)&m->d_state_mirror, m->h_state, 0);
 }
 
+// The same for the batched steps a model leads, descriptors and states in one
+// allocation.
+hipError_t alloc_batch_mirror(wici_model* m) {
+  if (m->h_seqs) return hipSuccess;
+  char* h = nullptr;
+  const size_t ds = kMaxBatch * sizeof(wici::SeqDesc);
+  if (hipError_t e = hipHostMalloc((void**)&h, ds + kMaxBatch * sizeof(DecodeState),
+                                   hipHostMallocMapped | hipHostMallocCoherent))
+    return e;
+  void* d = nullptr;
+  if (hipError_t e = hipHostGetDevicePointer(&d, h, 0)) {
+    (void)hipHostFree(h);
+    return e;
+  }
+  m->h_seqs = reinterpret_cast<wici::SeqDesc*>(h);
+  m->h_batch = reinterpret_cast<DecodeState*>(h + ds);
+  m->d_host_seqs = static_cast<wici::SeqDesc*>(d);
+  m->d_batch_mirror = reinterpret_cast<DecodeState*>(static_cast<char*>(d) + ds);
+  return hipSuccess;
+}
+
 // An in-launch merge (the decode attention's, or a batched product's split-K
 // sum) found its split blocks on different XCDs, so partials may have been read
 // before they were visible: the results of the step cannot be trusted and the
@@ -632,8 +660,8 @@ void arm_mirror(wici_model* m) {
 // milliseconds ends in an interrupt-driven sleep, which costs ~15 us per step).
 // The stream is polled as well: if it finishes or fails without `done`, returns
 // false (the caller then synchronises and reports what the stream says).
-bool wait_mirror(wici_model* m) {
-  const volatile int32_t* done = &m->h_state->done;
+bool wait_done(wici_model* m, const DecodeState* state) {
+  const volatile int32_t* done = &state->done;
   for (uint32_t i = 1;; ++i) {
     if (*done) {
       std::atomic_thread_fence(std::memory_order_acquire);
@@ -643,6 +671,7 @@ bool wait_mirror(wici_model* m) {
     __builtin_ia32_pause();
   }
 }
+bool wait_mirror(wici_model* m) { return wait_done(m, m->h_state); }
 
 // The step's final argmax kernel has written the new state into the pinned
 // mirror m->h_state as well.  Without logits to copy, the call returns once the
@@ -1075,7 +1104,6 @@ wici_status wici_decode_batch(wici_model* const* models, int32_t n, const int32_
   const size_t need = std::max((size_t)n * c.n_heads * L.nsplit * (c.head_dim + 2) * 4,
                                (size_t)n * c.vocab * 4);
   if (need > h_bytes) return fail(lead, WICI_E_ARG, "%d sequences exceed the batch scratch", n);
-  std::vector<wici::SeqDesc> sd(n);
   for (int b = 0; b < n; ++b) {
     wici_model* mb = models[b];
     if (!mb) return fail(lead, WICI_E_ARG, "NULL model %d", b);
@@ -1090,21 +1118,25 @@ wici_status wici_decode_batch(wici_model* const* models, int32_t n, const int32_
     if (mb->pos < 1) return fail(lead, WICI_E_STATE, "model %d: decode before prefill", b);
     if (t < 0 && !mb->have_token) return fail(lead, WICI_E_STATE, "model %d: no token", b);
     if (mb->pos + 1 > c.max_seq) return fail(lead, WICI_E_CAPACITY, "model %d is full", b);
-    sd[b].kv = mb->dkv;
-    sd[b].kv_layer_stride = mb->L.kv_layer_stride;
-    sd[b].table = mb->S<int32_t>(mb->L.table);
-    sd[b].state = mb->ds + mb->L.state;
-    sd[b].hist = mb->S<int32_t>(mb->L.hist);
   }
   // one sequence: its own step graph (the weight-streaming GEMVs), which the
   // batched matrix products cannot beat at a single row
   if (n == 1) return wici_decode_step(lead, tokens_in ? tokens_in[0] : -1, next_tokens, logits);
-  for (int b = 0; b < n; ++b)
-    if (tokens_in && tokens_in[b] >= 0)
-      HIP_TRY(lead, wici::launch_set_token(models[b]->ds + models[b]->L.state, tokens_in[b],
-                                           lead->stream));
-  HIP_TRY(lead, hipMemcpyAsync(lead->ds + L.seqs, sd.data(), n * sizeof(wici::SeqDesc),
-                               hipMemcpyHostToDevice, lead->stream));
+  // the step reads the descriptors from pinned memory and leaves the new states there
+  // (an earlier step has read its own by the time its call returned)
+  HIP_TRY(lead, alloc_batch_mirror(lead));
+  for (int b = 0; b < n; ++b) {
+    const wici_model* mb = models[b];
+    wici::SeqDesc& sd = lead->h_seqs[b];
+    sd.kv = mb->dkv;
+    sd.kv_layer_stride = mb->L.kv_layer_stride;
+    sd.table = mb->S<int32_t>(mb->L.table);
+    sd.state = mb->ds + mb->L.state;
+    sd.hist = mb->S<int32_t>(mb->L.hist);
+    sd.token = tokens_in ? tokens_in[b] : -1;
+    *static_cast<volatile int32_t*>(&lead->h_batch[b].done) = 0;
+  }
+  std::atomic_thread_fence(std::memory_order_release);
   const bool use_graph = lead->stream != nullptr && !(c.flags & WICI_FLAG_NO_GRAPH);
   if (use_graph) {
     auto it = lead->batch_graphs.find(n);
@@ -1126,14 +1158,17 @@ wici_status wici_decode_batch(wici_model* const* models, int32_t n, const int32_
   } else {
     HIP_TRY(lead, enqueue_decode_batch(lead, n));
   }
-  std::vector<DecodeState> st(n);
-  for (int b = 0; b < n; ++b)
-    HIP_TRY(lead, hipMemcpyAsync(&st[b], models[b]->ds + models[b]->L.state, sizeof(DecodeState),
-                                 hipMemcpyDeviceToHost, lead->stream));
-  if (logits)
-    HIP_TRY(lead, hipMemcpyAsync(logits, lead->ds + L.h, (size_t)n * c.vocab * 4,
-                                 hipMemcpyDeviceToHost, lead->stream));
-  HIP_TRY(lead, hipStreamSynchronize(lead->stream));
+  // without logits to copy the call returns once every row's state has landed, as a
+  // single decode step does
+  bool landed = logits == nullptr;
+  for (int b = 0; b < n && landed; ++b) landed = wait_done(lead, &lead->h_batch[b]);
+  if (!landed) {
+    if (logits)
+      HIP_TRY(lead, hipMemcpyAsync(logits, lead->ds + L.h, (size_t)n * c.vocab * 4,
+                                   hipMemcpyDeviceToHost, lead->stream));
+    HIP_TRY(lead, hipStreamSynchronize(lead->stream));
+  }
+  const DecodeState* st = lead->h_batch;
   if (st[0].fault) return placement_fault(lead);
   int bad = -1;
   for (int b = 0; b < n; ++b) {
@@ -1233,6 +1268,7 @@ void wici_destroy(wici_model* m) {
     (void)hipGraphDestroy(kv.second.first);
   }
   if (m->h_state) (void)hipHostFree(m->h_state);
+  if (m->h_seqs) (void)hipHostFree(m->h_seqs);
   delete m;
 }
 

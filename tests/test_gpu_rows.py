@@ -125,3 +125,43 @@ def test_batches_match_oracle(cuda_ok, name, weights, n):
     finally:
         for m in ms:
             m.close()
+
+
+def test_batch_groups_change_between_steps(cuda_ok):
+    """Descriptors, given tokens and returned states pass through one pinned buffer
+    per lead: groups of changing size, order and lead, tokens given for some
+    sequences only, with and without logits, each step's tokens and positions as when
+    every sequence decodes alone."""
+    from paper_2608_24204_amd.binding import WiciModel
+    cfg, w, _ = setup("narrow", "bf16")
+    kw = dict(max_seq=40, prefill_chunk=256)
+    rng = np.random.default_rng(5)
+    groups = [[0, 1, 2, 3, 4], [3, 1], [1, 3, 0], [4, 2, 0, 1], [3, 4], [0, 1, 2, 3, 4], [2, 0]]
+    given = [[int(t) if rng.random() < 0.5 else -1 for t in rng.integers(0, cfg.vocab, len(g))]
+             for g in groups]
+    lead = WiciModel(cfg, **kw)
+    ms = [lead]
+    try:
+        lead.load_weights(w)
+        ms += [WiciModel(cfg, share_weights_of=lead, **kw) for _ in range(4)]
+        ps = [rng.integers(0, cfg.vocab, 3 + b).astype(np.int32) for b in range(5)]
+
+        def run(step):
+            out = []
+            for m, p in zip(ms, ps):
+                m.reset_kv()
+                m.prefill(p)
+            for i, (g, t) in enumerate(zip(groups, given)):
+                out.append(step(i, [ms[b] for b in g], t))
+            return out, [m.position for m in ms]
+
+        def batched(i, models, toks):
+            got = WiciModel.decode_batch(models, toks, want_logits=i % 2 == 1)
+            return [int(t) for t in (got[0] if i % 2 == 1 else got)]
+
+        alone = run(lambda i, models, toks: [m.decode_step(t)[0] for m, t in zip(models, toks)])
+        assert run(batched) == alone
+        assert run(batched) == alone   # replayed graphs
+    finally:
+        for m in ms:
+            m.close()
