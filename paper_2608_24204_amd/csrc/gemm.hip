@@ -4,30 +4,23 @@
 // [out, in] layout, so both operands are contiguous along K, which is the layout
 // the gfx950 matrix cores consume (8 consecutive K values per lane).
 //
-// MFMA kernel.  A arrives as NT bf16 planes whose sum is the fp32 activation
-// (see ActBuf); the weights are exact bf16, so the kernel accumulates the NT
+// MFMA kernels.  A arrives as NT bf16 planes whose sum is the fp32 activation
+// (see ActBuf); the weights are exact bf16, so the kernels accumulate the NT
 // products A_p W^T with v_mfma_f32_16x16x32_bf16 and the result carries the
-// activation's precision, not bf16's.  Tiling:
-//  - a block of WM x WN wavefronts owns a (64 WM) x (64 WN) output tile, each
-//    wavefront a 64 x 64 sub-tile (4 x 4 matrix-core tiles, 64 accumulator
-//    registers);
-//  - both operands are staged through LDS in 32-deep K steps, double-buffered
-//    (64-byte rows with the 16-byte chunks XOR-swizzled by row, so that neither
-//    the stores nor the fragment reads hit the same bank twice); the next
-//    step's global loads are in flight while the current step's matrix ops run,
-//    one barrier a step;
-//  - tiles are numbered A-tile-row-major and dealt to the 8 XCDs in contiguous
-//    ranges (workgroups are dispatched round-robin over XCDs), so the blocks
-//    resident on one XCD share an A row-tile through that XCD's L2.
-// Two variants: bf16 weights go straight from global memory into LDS (k_gemm_dma);
-// 8-bit weights pass through registers, where their codes become bf16 values
-// (k_gemm_mfma).
+// activation's precision, not bf16's.  Operands are staged through LDS in 32-deep K
+// steps (64-byte rows with the 16-byte chunks XOR-swizzled by row, so that neither
+// the stores nor the fragment reads hit the same bank twice); tiles are dealt to the
+// 8 XCDs in contiguous ranges (workgroups are dispatched round-robin over XCDs), so
+// the blocks resident on one XCD share tiles through that XCD's L2.  Three variants:
+// tiles of bf16 weights (k_gemm_dma), tiles of 8-bit weights (k_gemm_q8), and few rows
+// (k_gemm_rows, either weights; k_gemm_skinny where K is no multiple of 128).
 //
 // Vector kernel: plain fp32 64x64 tiles, for fp32 weights / fp32 activations.
 #include "common.h"
 #include "kernels.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace wici {
 
@@ -65,198 +58,6 @@ __device__ __forceinline__ int lds_chunk(int row, int chunk) {
   return row * kLDK + 8 * (chunk ^ lds_swz(row));
 }
 
-// Q8 weights: a step of 32 along K is one quantisation block, so the codes go
-// through the matrix cores exactly (an integer in [-127, 127] is a bf16 value),
-// the NT products of a step are summed in a fresh accumulator, and that sum is
-// multiplied by the column's block scale and added: one scale multiply per
-// step and output, the products staying exact.
-template <int NT, int WM, int WN, int EPI, bool Q8>
-__global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(
-    const bf16_t* __restrict__ A, size_t a_plane, int lda, const void* __restrict__ Wv, int M,
-    int N, int K, int ks, float* __restrict__ C, size_t c_split, int ldc, ActBuf H, int ldh,
-    const unsigned short* __restrict__ S) {
-  constexpr int BM = 64 * WM, BN = 64 * WN, NTH = 64 * WM * WN;
-  constexpr int A_CHUNKS = NT * BM * (kBK / 8);  // 16-byte chunks per step
-  constexpr int W_CHUNKS = BN * (Q8 ? kBK / 16 : kBK / 8);
-  constexpr int WCPR = Q8 ? 2 : 4;               // weight chunks per row and step
-  const bf16_t* W = static_cast<const bf16_t*>(Wv);
-  const uint8_t* Wq = static_cast<const uint8_t*>(Wv);
-  constexpr int A_PER = (A_CHUNKS + NTH - 1) / NTH;
-  constexpr int W_PER = (W_CHUNKS + NTH - 1) / NTH;
-  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-  bf16_t* As = smem;                            // [2][NT][BM][kLDK]
-  bf16_t* Bs = smem + 2 * NT * BM * kLDK;       // [2][BN][kLDK]
-
-  // ---- tile of this block (A-row-major tile order, contiguous ranges per XCD) ----
-  const int n_mt = (M + BM - 1) / BM, n_nt = (N + BN - 1) / BN, T = n_mt * n_nt;
-  const int per_xcd = (T + 7) / 8;
-  const int t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (t >= T) return;
-  const int m0 = (t / n_nt) * BM, n0 = (t % n_nt) * BN;
-  // split K: block row y of the grid takes K range [y ks, (y + 1) ks) and writes
-  // its own output (c_split elements further on)
-  const int kbeg = blockIdx.y * ks;
-  C += blockIdx.y * c_split;
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int wm = wave / WN, wn = wave % WN;
-
-  uint4 ra[A_PER], rw[W_PER];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i) {
-      const int c = tid + i * NTH;
-      if (c < A_CHUNKS) {
-        const int p = c / (BM * 4), row = (c / 4) % BM, part = c % 4;
-        const int m = m0 + row;
-        ra[i] = m < M ? *reinterpret_cast<const uint4*>(A + p * a_plane + (size_t)m * lda + kbeg + k0 + part * 8)
-                      : make_uint4(0, 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < W_PER; ++i) {
-      const int c = tid + i * NTH;
-      if (c < W_CHUNKS) {
-        const int row = c / WCPR, part = c % WCPR, n = n0 + row;
-        if (Q8)
-          rw[i] = n < N ? *reinterpret_cast<const uint4*>(Wq + (size_t)n * K + kbeg + k0 + part * 16)
-                        : make_uint4(0x80808080u, 0x80808080u, 0x80808080u, 0x80808080u);
-        else
-          rw[i] = n < N ? *reinterpret_cast<const uint4*>(W + (size_t)n * K + kbeg + k0 + part * 8)
-                        : make_uint4(0, 0, 0, 0);
-      }
-    }
-  };
-  // Q8: the block scales of this lane's four output columns for step kt, loaded
-  // one step ahead together with that step's tiles
-  const int fr = lane & 15, fk = (lane >> 4) * 8;
-  unsigned short scq[4];
-  float scn[4];
-  auto sload = [&](int kt) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = min(n0 + wn * 64 + j * 16 + fr, N - 1);
-      scq[j] = S[(size_t)n * (K / 32) + kbeg / 32 + kt];
-    }
-  };
-  auto sfix = [&]() {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) scn[j] = (float)__builtin_bit_cast(_Float16, scq[j]);
-  };
-  auto sstore = [&](int s) {
-#pragma unroll
-    for (int i = 0; i < A_PER; ++i) {
-      const int c = tid + i * NTH;
-      if (c < A_CHUNKS) {
-        const int p = c / (BM * 4), row = (c / 4) % BM, part = c % 4;
-        *reinterpret_cast<uint4*>(As + ((size_t)s * NT + p) * BM * kLDK + lds_chunk(row, part)) = ra[i];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < W_PER; ++i) {
-      const int c = tid + i * NTH;
-      if (c < W_CHUNKS) {
-        const int row = c / WCPR, part = c % WCPR;
-        if (Q8) {
-          // 16 codes -> 16 bf16 values (code - 128, exact)
-          unsigned o[8];
-          const unsigned wv[4] = {rw[i].x, rw[i].y, rw[i].z, rw[i].w};
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const unsigned w = wv[e / 2], sh = 16 * (e & 1);
-            const float lo = (float)((w >> sh) & 0xffu) - 128.f;
-            const float hi = (float)((w >> (sh + 8)) & 0xffu) - 128.f;
-            o[e] = (__float_as_uint(lo) >> 16) | (__float_as_uint(hi) & 0xffff0000u);
-          }
-          bf16_t* bt = Bs + (size_t)s * BN * kLDK;
-          *reinterpret_cast<uint4*>(bt + lds_chunk(row, 2 * part)) = make_uint4(o[0], o[1], o[2], o[3]);
-          *reinterpret_cast<uint4*>(bt + lds_chunk(row, 2 * part + 1)) = make_uint4(o[4], o[5], o[6], o[7]);
-        } else {
-          *reinterpret_cast<uint4*>(Bs + (size_t)s * BN * kLDK + lds_chunk(row, part)) = rw[i];
-        }
-      }
-    }
-  };
-
-  floatx4_t acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-
-  const int KT = ks / kBK;
-  if (Q8) sload(0);
-  gload(0);
-  sstore(0);
-  if (Q8) sfix();
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    const int s = kt & 1;
-    if (kt + 1 < KT) {
-      if (Q8) sload(kt + 1);
-      gload((kt + 1) * kBK);
-    }
-    bf16x8_t bfr[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      bfr[j] = *reinterpret_cast<const bf16x8_t*>(Bs + (size_t)s * BN * kLDK +
-                                                  lds_chunk(wn * 64 + j * 16 + fr, fk / 8));
-    if constexpr (Q8) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        floatx4_t part[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) part[j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int p = 0; p < NT; ++p) {
-          const bf16x8_t af = *reinterpret_cast<const bf16x8_t*>(
-              As + ((size_t)s * NT + p) * BM * kLDK + lds_chunk(wm * 64 + i * 16 + fr, fk / 8));
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            part[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr[j], part[j], 0, 0, 0);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) acc[i][j][r] += part[j][r] * scn[j];
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < NT; ++p) {
-        bf16x8_t af[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          af[i] = *reinterpret_cast<const bf16x8_t*>(
-              As + ((size_t)s * NT + p) * BM * kLDK + lds_chunk(wm * 64 + i * 16 + fr, fk / 8));
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-      }
-    }
-    if (kt + 1 < KT) {
-      sstore(s ^ 1);
-      if (Q8) sfix();
-    }
-    __syncthreads();
-  }
-
-  // lane holds rows 4*(lane/16)+r and column lane%16 of each 16x16 tile
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm * 64 + i * 16 + (lane >> 4) * 4 + r;
-        const int n = n0 + wn * 64 + j * 16 + (lane & 15);
-        const float v = acc[i][j][r];
-        const float o = EPI == GEMV_SWIGLU ? pair_swap(v) : 0.f;
-        epi_out<EPI>(C, ldc, H, ldh, M, N, m, n, v, o);
-      }
-}
-
 // --------------------------------------------------------- MFMA, direct to LDS
 // bf16 weights: a K step's tiles go from global memory straight into LDS (buffer
 // loads to LDS: each lane's 16 bytes land at its wavefront's LDS base + 16 x lane,
@@ -282,6 +83,49 @@ __global__ __launch_bounds__(64 * WM * WN) void k_gemm_mfma(
 // one row and stores 16 bytes (fp32).  For SwiGLU the weight rows of a tile are
 // dealt so that a lane's four tiles are sixteen consecutive columns, i.e. eight
 // outputs, 16 bytes per term plane.
+// A lane's results of one output row m: columns 4 fc + r of each 16-column tile from n0
+// on, or (SwiGLU) 16 fc + 4 (j % 4) + r of the 64 of four tiles.  vec: the rows of C are
+// aligned to four values.
+template <int EPI, int TNW>
+__device__ __forceinline__ void store_rows(const floatx4_t (&acc)[TNW], float* C, int ldc,
+                                           const ActBuf& H, int ldh, int N, int m, int n0, int fc,
+                                           bool vec) {
+  if constexpr (EPI == GEMV_SWIGLU) {
+#pragma unroll
+    for (int j = 0; j < TNW; j += 4) {
+      const int n = n0 + j * 16 + fc * 16;
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const floatx4_t& c = acc[j + e / 2];
+        o[e] = silu(c[2 * (e & 1)]) * c[2 * (e & 1) + 1];
+      }
+      if (n + 16 <= N && ldh % 8 == 0) {
+        store_act8(H, (size_t)m * ldh + n / 2, o);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (n + 2 * e + 1 < N) store_act(H, (size_t)m * ldh + n / 2 + e, o[e]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < TNW; ++j) {
+      const int n = n0 + j * 16 + fc * 4;
+      float* p = C + (size_t)m * ldc + n;
+      if (vec && n + 4 <= N) {
+        floatx4_t v = acc[j];
+        if (EPI == GEMV_RESID) v = *reinterpret_cast<const floatx4_t*>(p) + v;
+        *reinterpret_cast<floatx4_t*>(p) = v;
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (n + r < N) p[r] = EPI == GEMV_RESID ? p[r] + acc[j][r] : acc[j][r];
+      }
+    }
+  }
+}
+
 __device__ __forceinline__ void dma16(const bf16_t* g, bf16_t* lds_wave) {
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds_wave, 16, 0, 0);
 }
@@ -439,47 +283,198 @@ k_gemm_dma(const bf16_t* __restrict__ A, size_t a_plane, int lda, const bf16_t* 
     step(kt + 1, b1, b0);
   }
 
-  // lane: row 16 i + fr, columns 4 fc + r of tile j (dealt: 16 fc + 4 (j % 4) + r of
-  // the 64 of four tiles)
   const bool vec = N % 4 == 0 && ldc % 4 == 0;
 #pragma unroll
   for (int i = 0; i < TMW; ++i) {
     const int m = m0 + wm * 16 * TMW + i * 16 + fr;
-    if (m >= M) continue;
-    if constexpr (DEAL) {
+    if (m < M) store_rows<EPI, TNW>(acc[i], C, ldc, H, ldh, N, m, n0 + wn * 16 * TNW, fc, vec);
+  }
+}
+
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+// 8 codes (q + 128) as 8 bf16 values q, exact: with its top bit flipped a code byte
+// is q in two's complement, which one instruction converts to fp32 (byte select and
+// sign extension included); the upper halves of two of those are the bf16 pair.
+__device__ __forceinline__ bf16x8_t q8_frag(u32x2_t c) {
+  unsigned o[4];
 #pragma unroll
-      for (int j = 0; j < TNW; j += 4) {
-        const int n = n0 + wn * 16 * TNW + j * 16 + fc * 16;
-        float o[8];
+  for (int h = 0; h < 2; ++h) {
+    const int w = (int)(c[h] ^ 0x80808080u);
+    const float f0 = (float)(int8_t)w, f1 = (float)(int8_t)(w >> 8);
+    const float f2 = (float)(int8_t)(w >> 16), f3 = (float)(w >> 24);
+    o[2 * h] = __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302u);
+    o[2 * h + 1] = __builtin_amdgcn_perm(__float_as_uint(f3), __float_as_uint(f2), 0x07060302u);
+  }
+  return __builtin_bit_cast(bf16x8_t, make_uint4(o[0], o[1], o[2], o[3]));
+}
+
+// ------------------------------------------------------------- MFMA, Q8 weights
+// The same product, schedule and epilogue for 8-bit weights, 128 x 128 tiles of four
+// 64 x 64 wavefronts.  A 32-deep step is one quantisation block: its products (all
+// terms) are summed in a fresh accumulator and added times the column's block scale,
+// so the codes go through the matrix cores as exact bf16 integers.  The step is bound
+// by the vector ALU (64 scale FMAs a wavefront and the code conversion) beside the
+// matrix cores, so what matters is that the two overlap: a row tile's FMAs stand
+// behind the next one's products, and the codes of the step after are converted once
+// per workgroup, 16 per thread, on their way from registers into LDS (converted by
+// each wavefront that reads them they cost twice that).  Scales go through LDS as
+// fp32, a pair of steps at a time.  Every load is unconditional (past the last step the
+// last one's again), so the compiler's own waits count exactly.
+template <int NT, int EPI>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_q8(
+    const bf16_t* __restrict__ A, size_t a_plane, int lda, const uint8_t* __restrict__ W,
+    const unsigned short* __restrict__ S, int M, int N, int K, int ks, float* __restrict__ C,
+    size_t c_split, int ldc, ActBuf H, int ldh) {
+  constexpr int BM = 128, BN = 128, NW = 4, TMW = 4, TNW = 4, STG = 2;
+  constexpr int PAP = 2, PA = NT * PAP;         // 16-byte units per lane: a plane of A, all of A
+  constexpr int ASTAGE = NT * BM * kLDK, WSTAGE = BN * kLDK;
+  constexpr bool DEAL = EPI == GEMV_SWIGLU;
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+  bf16_t* Ws = smem + STG * ASTAGE;                        // [2][BN][kLDK]
+  float* Sc = reinterpret_cast<float*>(Ws + 2 * WSTAGE);   // [2 pairs][2 steps][BN]
+
+  const int n_mt = (M + BM - 1) / BM, n_nt = (N + BN - 1) / BN;
+  const int T = n_mt * n_nt, per_xcd = (T + 7) / 8;
+  const int t = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (t >= T) return;
+  const int m0 = (t / n_nt) * BM, n0 = (t % n_nt) * BN;
+  const int kbeg = blockIdx.y * ks;
+  C += blockIdx.y * c_split;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int wm = wave >> 1, wn = wave & 1, fr = lane & 15, fc = lane >> 4;
+  const int KT = ks / kBK;  // even
+
+  auto w_swz = [](int row) { return DEAL ? (row >> 4) & 3 : lds_swz(row); };
+  const int r0 = wave * 16 + (lane >> 2);
+  const int offA = (int)(((size_t)r0 * lda + ((lane & 3) ^ lds_swz(r0)) * 8) * 2);
+  auto issue = [&](int stage, int kt) {
+    bf16_t* sb = smem + stage * ASTAGE;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const floatx4_t& c = acc[i][j + e / 2];
-          o[e] = silu(c[2 * (e & 1)]) * c[2 * (e & 1) + 1];
-        }
-        if (n + 16 <= N && ldh % 8 == 0) {
-          store_act8(H, (size_t)m * ldh + n / 2, o);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (n + 2 * e + 1 < N) store_act(H, (size_t)m * ldh + n / 2 + e, o[e]);
-        }
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < TNW; ++j) {
-        const int n = n0 + wn * 16 * TNW + j * 16 + fc * 4;
-        float* p = C + (size_t)m * ldc + n;
-        if (vec && n + 4 <= N) {
-          floatx4_t v = acc[i][j];
-          if (EPI == GEMV_RESID) v = *reinterpret_cast<const floatx4_t*>(p) + v;
-          *reinterpret_cast<floatx4_t*>(p) = v;
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (n + r < N) p[r] = EPI == GEMV_RESID ? p[r] + acc[i][j][r] : acc[i][j][r];
-        }
-      }
+    for (int i = 0; i < PA; ++i) {
+      const int rr = (i % PAP) * NW * 16, cnt = min(M - m0 - rr, NW * 16);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(
+          rsrc(A + (i / PAP) * a_plane + (size_t)(m0 + rr) * lda + kbeg,
+               cnt > 0 ? ((size_t)(cnt - 1) * lda + ks) * 2 : 0),
+          (__attribute__((address_space(3))) void*)(sb + (i * NW + wave) * 512), 16, offA,
+          kt * (kBK * 2), 0, 0);
     }
+  };
+  // this thread's half row of codes (16) per step, and its scale per pair of steps
+  const int wr = tid >> 1, wh = tid & 1, wrow = min(n0 + wr, N - 1);
+  const uint8_t* wsrc = W + (size_t)wrow * K + kbeg + wh * 16;
+  const unsigned short* ssrc = S + (size_t)wrow * (K / 32) + kbeg / 32 + wh;
+  typedef unsigned u32x4_v __attribute__((ext_vector_type(4)));
+  auto wload = [&](int kt) {
+    return *reinterpret_cast<const u32x4_v*>(wsrc + (size_t)min(kt, KT - 1) * kBK);
+  };
+  auto sload = [&](int pair) { return ssrc[2 * min(pair, KT / 2 - 1)]; };
+  auto wstore = [&](int buf, u32x4_v v) {
+    bf16_t* row = Ws + buf * WSTAGE + wr * kLDK;
+    *reinterpret_cast<bf16x8_t*>(row + 8 * ((2 * wh) ^ w_swz(wr))) = q8_frag(u32x2_t{v.x, v.y});
+    *reinterpret_cast<bf16x8_t*>(row + 8 * ((2 * wh + 1) ^ w_swz(wr))) = q8_frag(u32x2_t{v.z, v.w});
+  };
+  auto sstore = [&](int buf, unsigned short v) {
+    Sc[(buf * 2 + wh) * BN + wr] = (float)__builtin_bit_cast(_Float16, v);
+  };
+
+  floatx4_t acc[TMW][TNW];
+#pragma unroll
+  for (int i = 0; i < TMW; ++i)
+#pragma unroll
+    for (int j = 0; j < TNW; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  auto readW = [&](int buf, bf16x8_t (&b)[TNW]) {
+#pragma unroll
+    for (int j = 0; j < TNW; ++j) {
+      const int row = wn * 64 + (DEAL ? (fr >> 2) * 16 + j * 4 + (fr & 3) : j * 16 + fr);
+      b[j] = *reinterpret_cast<const bf16x8_t*>(Ws + buf * WSTAGE + row * kLDK + 8 * (fc ^ w_swz(row)));
+    }
+  };
+  auto readS = [&](int pairbuf, int h, floatx4_t (&d)[TNW]) {  // columns of this lane's results
+#pragma unroll
+    for (int j = 0; j < TNW; ++j)
+      d[j] = *reinterpret_cast<const floatx4_t*>(
+          Sc + (pairbuf * 2 + h) * BN + wn * 64 + (DEAL ? fc * 16 + j * 4 : j * 16 + fc * 4));
+  };
+  auto readA = [&](int stage, int i, bf16x8_t (&a)[NT]) {
+#pragma unroll
+    for (int p = 0; p < NT; ++p)
+      a[p] = *reinterpret_cast<const bf16x8_t*>(smem + stage * ASTAGE +
+                                                lds_chunk(p * BM + wm * 64 + i * 16 + fr, fc));
+  };
+  auto mult = [&](const bf16x8_t (&a)[NT], const bf16x8_t (&b)[TNW], floatx4_t (&q)[TNW]) {
+#pragma unroll
+    for (int p = 0; p < NT; ++p)
+#pragma unroll
+      for (int j = 0; j < TNW; ++j)
+        q[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            b[j], a[p], p ? q[j] : floatx4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+  };
+  auto fold = [&](int i, const floatx4_t (&q)[TNW], const floatx4_t (&d)[TNW]) {
+#pragma unroll
+    for (int j = 0; j < TNW; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] += q[j][r] * d[j][r];
+  };
+
+  issue(0, 0);
+  u32x4_v rw = wload(0);
+  unsigned short rs = sload(0);
+  wstore(0, rw);
+  sstore(0, rs);
+  rw = wload(1);
+  rs = sload(1);
+  issue(1, 1);
+  wait_vm_lgkm<0>();
+  __builtin_amdgcn_s_barrier();
+  bf16x8_t b0[TNW], b1[TNW], a0[NT], a1[NT];
+  floatx4_t d[TNW], q0[TNW], q1[TNW];
+  readW(0, b0);
+  readA(0, 0, a0);
+  auto step = [&](int kt, auto odd_t, const bf16x8_t (&b)[TNW], bf16x8_t (&bn)[TNW]) {
+    constexpr int ODD = decltype(odd_t)::value;
+    const int pb = (kt >> 1) & 1;
+    readS(pb, ODD, d);
+    // the next step's codes (and, once a pair, the next pair's scales) into LDS; the
+    // ones after that requested
+    wstore(1 - ODD, rw);
+    if (ODD) sstore(1 - pb, rs);
+    rw = wload(kt + 2);
+    if (ODD) rs = sload((kt >> 1) + 2);
+    readA(ODD, 1, a1);
+    __builtin_amdgcn_sched_barrier(0);
+    mult(a0, b, q0);
+    readA(ODD, 2, a0);
+    mult(a1, b, q1);
+    fold(0, q0, d);
+    __builtin_amdgcn_sched_barrier(0);
+    readA(ODD, 3, a1);
+    mult(a0, b, q0);
+    fold(1, q1, d);
+    __builtin_amdgcn_sched_barrier(0);
+    // the next stage of A has landed (this step's code and scale loads may be in
+    // flight), every wavefront has read this one and written the next codes
+    wait_vm_lgkm<1 + ODD>();
+    __builtin_amdgcn_s_barrier();
+    issue(ODD, min(kt + 2, KT - 1));
+    readW(1 - ODD, bn);
+    readA(1 - ODD, 0, a0);
+    __builtin_amdgcn_sched_barrier(0);
+    mult(a1, b, q1);
+    fold(2, q0, d);
+    fold(3, q1, d);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int kt = 0; kt < KT; kt += 2) {
+    step(kt, std::integral_constant<int, 0>{}, b0, b1);
+    step(kt + 1, std::integral_constant<int, 1>{}, b1, b0);
+  }
+  wait_vm_lgkm<0>();  // the last refills
+
+  const bool vec = N % 4 == 0 && ldc % 4 == 0;
+#pragma unroll
+  for (int i = 0; i < TMW; ++i) {
+    const int m = m0 + wm * 64 + i * 16 + fr;
+    if (m < M) store_rows<EPI, TNW>(acc[i], C, ldc, H, ldh, N, m, n0 + wn * 64, fc, vec);
   }
 }
 
@@ -637,29 +632,12 @@ __device__ __forceinline__ int rows_swz(int row, int c) {
   return CH == 16 ? c ^ (row & 15) : c ^ ((row >> 1) & 7);
 }
 
-typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 // Two LDS dwords, as a plain vector load: a load through a struct (uint2) or a bit
 // cast carries no type information, and the compiler then waits for every
 // direct-to-LDS load in flight first (s_waitcnt vmcnt(0), which empties the ring).
 __device__ __forceinline__ u32x2_t lds_b64(const bf16_t* p) {
   const u32x2_t v = *reinterpret_cast<const u32x2_t*>(p);
   return v;
-}
-
-// 8 codes (q + 128) as 8 bf16 values q, exact: with its top bit flipped a code byte
-// is q in two's complement, which one instruction converts to fp32 (byte select and
-// sign extension included); the upper halves of two of those are the bf16 pair.
-__device__ __forceinline__ bf16x8_t q8_frag(u32x2_t c) {
-  unsigned o[4];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int w = (int)(c[h] ^ 0x80808080u);
-    const float f0 = (float)(int8_t)w, f1 = (float)(int8_t)(w >> 8);
-    const float f2 = (float)(int8_t)(w >> 16), f3 = (float)(w >> 24);
-    o[2 * h] = __builtin_amdgcn_perm(__float_as_uint(f1), __float_as_uint(f0), 0x07060302u);
-    o[2 * h + 1] = __builtin_amdgcn_perm(__float_as_uint(f3), __float_as_uint(f2), 0x07060302u);
-  }
-  return __builtin_bit_cast(bf16x8_t, make_uint4(o[0], o[1], o[2], o[3]));
 }
 
 template <int NT, int TM, int WN, int KC, int STG, int EPI, bool Q8>
@@ -981,24 +959,22 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, i
 }
 
 // ------------------------------------------------------------------- launchers
-template <int NT, int WM, int WN, int EPI, bool Q8>
-static hipError_t gemm_mfma_launch(const ActBuf& A, int lda, const void* W, int M, int N, int K,
-                                   float* C, int ldc, const ActBuf& H, int ldh, hipStream_t st,
-                                   int nsplit = 1, size_t c_split = 0) {
-  constexpr int BM = 64 * WM, BN = 64 * WN;
-  const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  const int grid = (tiles + 7) / 8 * 8;
-  const size_t lds = (size_t)2 * (NT * BM + BN) * kLDK * sizeof(bf16_t);
-  const unsigned short* S =
-      Q8 ? reinterpret_cast<const unsigned short*>(static_cast<const char*>(W) +
-                                                   q8_scale_offset(N, K))
-         : nullptr;
-  auto fn = &k_gemm_mfma<NT, WM, WN, EPI, Q8>;
+template <int NT, int EPI>
+static hipError_t gemm_q8_launch(const ActBuf& A, int lda, const void* W, int M, int N, int K,
+                                 float* C, int ldc, const ActBuf& H, int ldh, hipStream_t st,
+                                 int nsplit = 1, size_t c_split = 0) {
+  if (K % (2 * kBK * nsplit)) return hipErrorInvalidValue;  // K ranges of whole pairs of steps
+  const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
+  const size_t lds = (2 * NT * 128 + 2 * 128) * kLDK * sizeof(bf16_t) + 4 * 128 * sizeof(float);
+  const unsigned short* S = reinterpret_cast<const unsigned short*>(
+      static_cast<const char*>(W) + q8_scale_offset(N, K));
+  auto fn = &k_gemm_q8<NT, EPI>;
   if (lds > 65536)
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  hipLaunchKernelGGL(fn, dim3(grid, nsplit), dim3(64 * WM * WN), lds, st, A.planes,
-                     A.plane_stride, lda, W, M, N, K, K / nsplit, C, c_split, ldc, H, ldh, S);
+  hipLaunchKernelGGL(fn, dim3((tiles + 7) / 8 * 8, nsplit), dim3(256), lds, st, A.planes,
+                     A.plane_stride, lda, static_cast<const uint8_t*>(W), S, M, N, K, K / nsplit, C,
+                     c_split, ldc, H, ldh);
   return hipGetLastError();
 }
 
@@ -1104,9 +1080,9 @@ static hipError_t gemm_mfma(const ActBuf& A, int lda, const void* W, int M, int 
     }
   }
   switch (A.nt) {
-    case 1: return gemm_mfma_launch<1, 2, 2, EPI, Q8>(A, lda, W, M, N, K, C, ldc, H, ldh, st);
-    case 2: return gemm_mfma_launch<2, 2, 2, EPI, Q8>(A, lda, W, M, N, K, C, ldc, H, ldh, st);
-    case 3: return gemm_mfma_launch<3, 2, 2, EPI, Q8>(A, lda, W, M, N, K, C, ldc, H, ldh, st);
+    case 1: return gemm_q8_launch<1, EPI>(A, lda, W, M, N, K, C, ldc, H, ldh, st);
+    case 2: return gemm_q8_launch<2, EPI>(A, lda, W, M, N, K, C, ldc, H, ldh, st);
+    case 3: return gemm_q8_launch<3, EPI>(A, lda, W, M, N, K, C, ldc, H, ldh, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1209,8 +1185,7 @@ static hipError_t gemm_split_nt(int wt, const ActBuf& A, int lda, const void* W,
                                 int K, int nsplit, float* P, size_t p_split, hipStream_t st) {
   const ActBuf none{};
   if (wt == W_Q8)
-    return gemm_mfma_launch<NT, 2, 2, GEMV_STORE, true>(A, lda, W, M, N, K, P, N, none, 0, st,
-                                                         nsplit, p_split);
+    return gemm_q8_launch<NT, GEMV_STORE>(A, lda, W, M, N, K, P, N, none, 0, st, nsplit, p_split);
   return gemm_dma_pick<NT, GEMV_STORE>(A, lda, W, M, N, K, P, N, none, 0, st, nsplit, p_split);
 }
 
