@@ -662,7 +662,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   static_assert(kRowsKC % KC == 0 && (CHA == 8 || CHA == 16) && (CHW == 8 || CHW == 16), "slices");
   static_assert(!Q8 || (KC == 128 && WN <= 2), "four block scales per row and slice");
   static_assert(STG >= 2 && STG <= 4, "stage ring of 2-4");
-  constexpr int SG = KC / kBK <= 2 || NT * TM <= 6 ? KC / kBK : 2;
+  // 32-deep steps whose fragments are read together, as the registers allow
+  constexpr auto group = [](int n) { return n * (NT * TM + WN) * 4 + TM * WN * 4 <= 192; };
+  constexpr int SG = Q8 ? (NT * TM <= 6 ? 4 : 2)
+                     : group(KC / kBK) ? KC / kBK : group(2) ? 2 : 1;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
 
   const int T = (N + BN - 1) / BN;
@@ -757,6 +760,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                 xb + ((p * 16 * TM + xr) * CHA + rows_swz<CHA>(xr, 4 * st + g)) * 8);
           }
       }
+      // the group's reads stay ahead of its products (the compiler otherwise deals them out
+      // two or three at a time with a wait for each: 8B gate/up at 128 rows 94 -> 86 us)
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int u = 0; u < SG; ++u) {
         if constexpr (Q8) {
@@ -816,6 +822,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     compute(kt % STG);
   }
 
+  auto out_row = [&](int i, int r) { return i * 16 + 4 * g + r; };
+  auto out_col = [&](int j) { return n0 + (wave * WN + j) * 16 + fr; };
+  // The residual rows are requested at once (clamped into C), in the split that adds
+  // them: read where they are added, each value waited out a round trip of its own
+  // (8B O at 64 rows 18.6 -> 15.9 us, down 40.3 -> 37.3 with the reads above; more than
+  // 96 rows leave no registers for them).
+  constexpr bool PRE = EPI == GEMV_RESID && TM <= 6;
+  float old[TM][WN][4];
+  auto load_old = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          old[i][j][r] = C[(size_t)min(out_row(i, r), M - 1) * ldc + min(out_col(j), N - 1)];
+  };
+  if (PRE && nsplit == 1) load_old();
   if (nsplit > 1) {
     __shared__ int s_last;
     constexpr int FR = TM * WN;  // accumulator tiles of a wavefront
@@ -851,6 +875,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       const int xo = __builtin_amdgcn_raw_buffer_load_b32(rs, (32 + lane) * 4, 0, 1);
       if (xo != me || drill) *fault = 1;
     }
+    if (PRE) load_old();
     floatx4_t sum[TM][WN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -888,17 +913,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int j = 0; j < WN; ++j) acc[i][j] = sum[i][j];
   }
-  // epilogue (lane: rows 16 i + 4 g + r, column n0 + 16 (WN wave + j) + fr)
+  // epilogue
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < WN; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int m = i * 16 + 4 * g + r, n = n0 + (wave * WN + j) * 16 + fr;
+        const int m = out_row(i, r), n = out_col(j);
         const float v = acc[i][j][r];
-        const float o = EPI == GEMV_SWIGLU ? pair_swap(v) : 0.f;
-        epi_out<EPI>(C, ldc, H, ldh, M, N, m, n, v, o);
+        if (PRE) {
+          if (m < M && n < N) C[(size_t)m * ldc + n] = old[i][j][r] + v;
+        } else {
+          const float o = EPI == GEMV_SWIGLU ? pair_swap(v) : 0.f;
+          epi_out<EPI>(C, ldc, H, ldh, M, N, m, n, v, o);
+        }
       }
 }
 
