@@ -776,12 +776,19 @@ __global__ __launch_bounds__(256) void k_attn_prefill_mfma(const float* __restri
   const float scale = 1.0f / sqrtf((float)HD);
   bf16x8_t qf[NT][DS];
   {
-    const float* qr = qkv + (size_t)(qvalid ? tq : 0) * width + (size_t)h * HD;
+    // (loaded whatever the row, the last one past the chunk: loads under a condition
+    // became branches that each waited out a memory round trip, 32 of them in turn)
+    const float* qr = qkv + (size_t)min(tq, T - 1) * width + (size_t)h * HD + 8 * lg;
+    floatx4_t qv[DS][2];
+#pragma unroll
+    for (int s = 0; s < DS; ++s)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) qv[s][e] = *reinterpret_cast<const floatx4_t*>(qr + 32 * s + 4 * e);
 #pragma unroll
     for (int s = 0; s < DS; ++s) {
       float v[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = qvalid ? qr[32 * s + 8 * lg + e] * scale : 0.f;
+      for (int e = 0; e < 8; ++e) v[e] = qvalid ? qv[s][e / 4][e % 4] * scale : 0.f;
 #pragma unroll
       for (int p = 0; p < NT; ++p) {
 #pragma unroll
@@ -963,21 +970,23 @@ __global__ __launch_bounds__(256) void k_attn_prefill_mfma(const float* __restri
   tload(0, pa0, pa1);
   gload(WICI_SET_A, 0, pa0, pa1);
   tload(BKEY, pb0, pb1);
-  gload(WICI_SET_B, BKEY, pb0, pb1);
   tload(2 * BKEY, pa0, pa1);
+  gload(WICI_SET_B, BKEY, pb0, pb1);
   for (int kb = 0; kb < kend; kb += 2 * BKEY) {
     __syncthreads();          // previous block's readers are done with LDS
     sstore(WICI_SET_A);
     __syncthreads();
+    tload(kb + 3 * BKEY, pb0, pb1);  // first: its wait leaves the keys and values in flight
     gload(WICI_SET_A, kb + 2 * BKEY, pa0, pa1);
-    tload(kb + 3 * BKEY, pb0, pb1);
+    __builtin_amdgcn_sched_barrier(0);
     compute(kb);
     if (kb + BKEY >= kend) break;
     __syncthreads();
     sstore(WICI_SET_B);
     __syncthreads();
-    gload(WICI_SET_B, kb + 3 * BKEY, pb0, pb1);
     tload(kb + 4 * BKEY, pa0, pa1);
+    gload(WICI_SET_B, kb + 3 * BKEY, pb0, pb1);
+    __builtin_amdgcn_sched_barrier(0);
     compute(kb + BKEY);
   }
 #undef WICI_SET_A
