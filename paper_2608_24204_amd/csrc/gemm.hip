@@ -1275,6 +1275,15 @@ static hipError_t gemm_rows(const ActBuf& A, int lda, const void* W, int M, int 
   // are 128 deep up to 32 rows and 64 from 33 on (48 rows: gate/up 60.5 us at 128),
   // the stages as many as leave two workgroups per CU, or one with wide slices.
   const bool wide = EPI != GEMV_RESID && N >= 192 * 128;
+  // Also, from 17 rows of bf16 weights, where the K ranges that give 192 workgroups are
+  // still 1024 deep: QKV 19.4 -> 16.4 us at 32 rows, 23.1 -> 20.0 at 48, 27.1 -> 23.2 at
+  // 64, down 27.4 -> 26.6, 33.1 -> 29.0 and 37.3 -> 32.8 (at 16 rows 25.2 against 25.3; O,
+  // whose ranges would be 512 deep, 16.5 -> 22.0 at 48).
+  auto deep = [&]() {
+    if (!part || !sync || !fault) return false;
+    const int n = gemm_rows_splits((M + 15) / 16, 128, N, K, part_floats);
+    return (long)((N + 127) / 128) * n >= 192 && K / n >= 1024;
+  };
   if constexpr (Q8) {
     if (M <= 16) return go(RowsShape<1, 1, 128, 4>{});
     if (M <= 32) return wide ? go(RowsShape<2, 2, 128, 3>{}) : go(RowsShape<2, 1, 128, 3>{});
@@ -1282,9 +1291,9 @@ static hipError_t gemm_rows(const ActBuf& A, int lda, const void* W, int M, int 
     return wide ? go(RowsShape<4, 2, 128, NT <= 2 ? 3 : 2>{}) : go(RowsShape<4, 1, 128, 2>{});
   } else {
     if (M <= 16) return wide ? go(RowsShape<1, 2, 128, 3>{}) : go(RowsShape<1, 1, 128, 3>{});
-    if (M <= 32) return wide ? go(RowsShape<2, 2, 64, 4>{}) : go(RowsShape<2, 1, 128, 3>{});
-    if (M <= 48) return wide ? go(RowsShape<3, 2, 64, 3>{}) : go(RowsShape<3, 1, 64, 3>{});
-    if (M <= 64) return wide ? go(RowsShape<4, 2, 64, 3>{}) : go(RowsShape<4, 1, 64, 3>{});
+    if (M <= 32) return wide || deep() ? go(RowsShape<2, 2, 64, 4>{}) : go(RowsShape<2, 1, 128, 3>{});
+    if (M <= 48) return wide || deep() ? go(RowsShape<3, 2, 64, 3>{}) : go(RowsShape<3, 1, 64, 3>{});
+    if (M <= 64) return wide || deep() ? go(RowsShape<4, 2, 64, 3>{}) : go(RowsShape<4, 1, 64, 3>{});
     if (M <= 96) return go(RowsShape<6, 2, 64, 3>{});
     return go(RowsShape<8, 2, 64, 2>{});
   }

@@ -19,12 +19,14 @@ pytestmark = pytest.mark.gpu
 
 # narrow: every product split along K (3 and 9 ranges of 128 among them), vocab and
 # QKV rows no multiple of a tile; wide: gate/up and LM head past 192 x 128 rows, the
-# LM head's last tile ragged
+# LM head's last tile ragged; deep: the down product in K ranges of 1024 on 128 weight rows
 CFGS = {
     "narrow": configs.ModelConfig(name="t_rows", key=110, n_layers=2, d_model=384, n_heads=4,
                                   n_kv_heads=2, head_dim=64, ffn_dim=1152, vocab=1003),
     "wide": configs.ModelConfig(name="t_rows_wide", key=111, n_layers=2, d_model=256, n_heads=2,
                                 n_kv_heads=1, head_dim=128, ffn_dim=12416, vocab=24601),
+    "deep": configs.ModelConfig(name="t_rows_deep", key=112, n_layers=1, d_model=2048, n_heads=4,
+                                n_kv_heads=1, head_dim=128, ffn_dim=12288, vocab=1003),
 }
 
 
