@@ -171,8 +171,7 @@ wici_status wici_load_weights(wici_model* m, const wici_tensor* tensors, int32_t
  * n_tokens < 1, an id outside [0, vocab)), WICI_E_STATE (weights incomplete),
  * WICI_E_CAPACITY (position + n_tokens > max_seq), WICI_E_NUMERIC (the
  * positions were still appended; no token is returned, so a following decode
- * step needs an explicit token_in), WICI_E_HIP (a HIP error, or, for few rows,
- * misplaced splits of a product as for wici_decode_batch; sticky). */
+ * step needs an explicit token_in). */
 wici_status wici_prefill(wici_model* m, const int32_t* tokens, int32_t n_tokens,
                          int32_t* first_token, float* logits);
 

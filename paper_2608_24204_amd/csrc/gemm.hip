@@ -610,7 +610,10 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(const bf16_t* __restrict__ 
 // lane's column).  A slice's scales go through LDS with its stage (in registers
 // the compiler waited for every load in flight before each slice).
 //
-// Products with few weight rows are split along K over grid slots: the splits
+// Products with few weight rows are split along K over grid slots.  With c_split
+// each split writes its own output, c_split elements after the one before, and the
+// next kernel adds them (prompts: nothing depends on where a workgroup runs).
+// Without it they are summed in the launch: the splits
 // of a tile occupy workgroup indices of one residue mod 8, so they run on
 // one XCD (dispatch deals workgroups to the XCDs in turn) and exchange their
 // partials through its L2, as the decode attention merge does: each split
@@ -644,8 +647,8 @@ template <int NT, int TM, int WN, int KC, int STG, int EPI, bool Q8>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_rows(const bf16_t* __restrict__ A, size_t a_plane,
                                                    int lda, const void* __restrict__ Wv, int M,
                                                    int N, int K, int nsplit, int ks,
-                                                   float* __restrict__ C, int ldc, ActBuf H,
-                                                   int ldh, floatx4_t* __restrict__ part,
+                                                   float* __restrict__ C, size_t c_split, int ldc,
+                                                   ActBuf H, int ldh, floatx4_t* __restrict__ part,
                                                    int* __restrict__ sync,
                                                    int* __restrict__ fault, int drill,
                                                    const unsigned short* __restrict__ S) {
@@ -840,7 +843,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           old[i][j][r] = C[(size_t)min(out_row(i, r), M - 1) * ldc + min(out_col(j), N - 1)];
   };
   if (PRE && nsplit == 1) load_old();
-  if (nsplit > 1) {
+  if (EPI == GEMV_STORE && c_split) {
+    C += split * c_split;
+  } else if (nsplit > 1) {
     __shared__ int s_last;
     constexpr int FR = TM * WN;  // accumulator tiles of a wavefront
     floatx4_t* slab = part + ((size_t)(t * nsplit + split) * 4 + wave) * FR * 64;
@@ -1153,8 +1158,8 @@ static hipError_t gemm_skinny(const ActBuf& A, int lda, const void* W, int M, in
 
 template <int NT, int TM, int WN, int KC, int STG, int EPI, bool Q8>
 static hipError_t gemm_rows_launch(const ActBuf& A, int lda, const void* W, int M, int N, int K,
-                                   int nsplit, float* C, int ldc, const ActBuf& H, int ldh,
-                                   float* part, int* sync, int* fault, hipStream_t st,
+                                   int nsplit, float* C, size_t c_split, int ldc, const ActBuf& H,
+                                   int ldh, float* part, int* sync, int* fault, hipStream_t st,
                                    int drill = 0) {
   const int T = (N + 64 * WN - 1) / (64 * WN);
   const int grid = 8 * ((T + 7) / 8) * nsplit;
@@ -1170,7 +1175,7 @@ static hipError_t gemm_rows_launch(const ActBuf& A, int lda, const void* W, int 
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(fn, dim3(grid), dim3(256), lds, st, A.planes, A.plane_stride, lda, W, M, N, K,
-                     nsplit, K / nsplit, C, ldc, H, ldh, reinterpret_cast<floatx4_t*>(part), sync,
+                     nsplit, K / nsplit, C, c_split, ldc, H, ldh, reinterpret_cast<floatx4_t*>(part), sync,
                      fault, drill, S);
   return hipGetLastError();
 }
@@ -1188,60 +1193,18 @@ static hipError_t gemm_f32(const ActBuf& A, int lda, const WT* W, int M, int N, 
   return hipGetLastError();
 }
 
-// Split K for products with too few output tiles to fill the chip: as many
-// splits (at most four) as still leave at most two blocks per CU (512), each at least
-// 256 deep.  bf16 weights: or another count, up to eight, that tile_time puts at
-// least 12% below that (8B down at 700 rows 199 us in two ranges, 172 in eight; 32B
-// down at 2048 rows, whose 320 tiles leave 512 places unevenly filled, 1267 us whole
-// and 1037 in four ranges).
-int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split) {
-  if (nt < 1 || M <= 32 || (wt != W_BF16 && wt != W_Q8)) return 1;
-  auto fits = [&](int n) { return K % (2 * kBK * n) == 0 && K / n >= 256; };
-  const int bn = wt == W_BF16 && M >= 1024 ? 256 : 128;
-  const int tiles = ((M + 127) / 128) * ((N + bn - 1) / bn);
-  int n = std::max(1, std::min({max_split, 4, 512 / std::max(tiles, 1)}));
-  while (n > 1 && !fits(n)) --n;
-  if (wt == W_Q8) return n;
-  auto time = [&](int s) { return tile_time(tile_shape(nt, M, N, K, s), nt, M, N, K, s); };
-  int best = n;
-  for (int s = 1; s <= std::min(max_split, 8); ++s)
-    if ((s == 1 || fits(s)) && time(s) < time(best)) best = s;
-  return time(best) < 0.88f * time(n) ? best : n;
-}
-
-template <int NT>
-static hipError_t gemm_split_nt(int wt, const ActBuf& A, int lda, const void* W, int M, int N,
-                                int K, int nsplit, float* P, size_t p_split, hipStream_t st) {
-  const ActBuf none{};
-  if (wt == W_Q8)
-    return gemm_q8_launch<NT, GEMV_STORE>(A, lda, W, M, N, K, P, N, none, 0, st, nsplit, p_split);
-  return gemm_dma_pick<NT, GEMV_STORE>(A, lda, W, M, N, K, P, N, none, 0, st, nsplit, p_split);
-}
-
-hipError_t launch_gemm_split(int wt, const ActBuf& A, int lda, const void* W, int M, int N, int K,
-                             int nsplit, float* P, size_t p_split, hipStream_t st) {
-  if (nsplit < 1 || K % (2 * kBK * nsplit) || M <= 32 || (wt != W_BF16 && wt != W_Q8))
-    return hipErrorInvalidValue;
-  switch (A.nt) {
-    case 1: return gemm_split_nt<1>(wt, A, lda, W, M, N, K, nsplit, P, p_split, st);
-    case 2: return gemm_split_nt<2>(wt, A, lda, W, M, N, K, nsplit, P, p_split, st);
-    case 3: return gemm_split_nt<3>(wt, A, lda, W, M, N, K, nsplit, P, p_split, st);
-    default: return hipErrorInvalidValue;
-  }
-}
-
-// Splits along K for the few-rows kernel: the fewest (up to 16) that give at
+// Splits along K for the few-rows kernel: the fewest (up to `most`) that give at
 // least 192 workgroups of bn weight rows with whole 128-deep slices, as far as the
 // partials (tm 16-row tiles) fit `part_floats` and the tiles the sync lines.
 // (Measured at 16 rows on the 8B shapes, bf16: QKV 2 splits 12.6 us, 4 13.3; O 4
 // splits 9.9 us, 8 10.3; down 4 splits 24.8 us, 7 27.3; at 48 rows QKV 2 splits
 // 19.1 us, 8 20.0: more, shorter workgroups pay more in pipeline fill and in the
 // sum.)
-static int gemm_rows_splits(int tm, int bn, int N, int K, size_t part_floats) {
+static int gemm_rows_splits(int tm, int bn, int N, int K, size_t part_floats, int most) {
   const int T = (N + bn - 1) / bn;
   if (T > kRowsMaxTiles) return 1;
   int best = 1;
-  for (int s = 2; s <= 16 && T * best < 192; ++s) {
+  for (int s = 2; s <= most && T * best < 192; ++s) {
     if (K % (s * kRowsKC)) continue;
     if ((size_t)T * s * bn * 16 * tm > part_floats) break;
     best = s;
@@ -1256,47 +1219,33 @@ struct RowsShape {
   static constexpr int TM = TM_, WN = WN_, KC = KC_, STG = STG_;
 };
 
-template <int NT, int EPI, bool Q8>
-static hipError_t gemm_rows(const ActBuf& A, int lda, const void* W, int M, int N, int K, float* C,
-                            int ldc, const ActBuf& H, int ldh, float* part, size_t part_floats,
-                            int* sync, int* fault, hipStream_t st, bool drill) {
-  auto go = [&](auto shape) {
-    using R = decltype(shape);
-    const int nsplit = part && sync && fault
-                           ? gemm_rows_splits(R::TM, 64 * R::WN, N, K, part_floats) : 1;
-    return gemm_rows_launch<NT, R::TM, R::WN, R::KC, R::STG, EPI, Q8>(
-        A, lda, W, M, N, K, nsplit, C, ldc, H, ldh, part, sync, fault, st, drill);
+// 16-row tiles, 64-row column tiles per workgroup and K ranges of the few-rows kernel.
+struct RowsPlan {
+  int tm, wn, nsplit;
+};
+
+static RowsPlan rows_plan(int wt, int epi, int M, int N, int K, size_t part_floats, int most) {
+  const bool q8 = wt == W_Q8;
+  const int tm = M <= 64 ? (M + 15) / 16 : M <= 96 ? 6 : 8;
+  auto plan = [&](int wn) {
+    return RowsPlan{tm, wn, gemm_rows_splits(tm, 64 * wn, N, K, part_floats, most)};
   };
+  if (tm > 4) return plan(2);
   // 128 weight rows per workgroup (each activation fragment read for twice the
   // columns) where that alone still gives 192 workgroups: 8B gate/up, bf16, 43.2 ->
   // 40.2 us at 16 rows, 49.2 -> 42.7 at 32, 55.5 -> 47.4 at 48, 62.3 -> 55.1 at 64;
   // Q8 43.8 -> 39.6 at 32 and 78 -> 66 at 64, but 31.8 -> 33.3 at 8 and 47.8 -> 49.5
-  // at 48.  Narrower products keep 64 (O at 48 rows 15.6 against 17.9 us).  Slices
-  // are 128 deep up to 32 rows and 64 from 33 on (48 rows: gate/up 60.5 us at 128),
-  // the stages as many as leave two workgroups per CU, or one with wide slices.
-  const bool wide = EPI != GEMV_RESID && N >= 192 * 128;
+  // at 48.  Narrower products keep 64 (O at 48 rows 15.6 against 17.9 us).
+  if (epi != GEMV_RESID && N >= 192 * 128 && !(q8 && (tm == 1 || tm == 3))) return plan(2);
   // Also, from 17 rows of bf16 weights, where the K ranges that give 192 workgroups are
   // still 1024 deep: QKV 19.4 -> 16.4 us at 32 rows, 23.1 -> 20.0 at 48, 27.1 -> 23.2 at
   // 64, down 27.4 -> 26.6, 33.1 -> 29.0 and 37.3 -> 32.8 (at 16 rows 25.2 against 25.3; O,
   // whose ranges would be 512 deep, 16.5 -> 22.0 at 48).
-  auto deep = [&]() {
-    if (!part || !sync || !fault) return false;
-    const int n = gemm_rows_splits((M + 15) / 16, 128, N, K, part_floats);
-    return (long)((N + 127) / 128) * n >= 192 && K / n >= 1024;
-  };
-  if constexpr (Q8) {
-    if (M <= 16) return go(RowsShape<1, 1, 128, 4>{});
-    if (M <= 32) return wide ? go(RowsShape<2, 2, 128, 3>{}) : go(RowsShape<2, 1, 128, 3>{});
-    if (M <= 48) return go(RowsShape<3, 1, 128, 2>{});
-    return wide ? go(RowsShape<4, 2, 128, NT <= 2 ? 3 : 2>{}) : go(RowsShape<4, 1, 128, 2>{});
-  } else {
-    if (M <= 16) return wide ? go(RowsShape<1, 2, 128, 3>{}) : go(RowsShape<1, 1, 128, 3>{});
-    if (M <= 32) return wide || deep() ? go(RowsShape<2, 2, 64, 4>{}) : go(RowsShape<2, 1, 128, 3>{});
-    if (M <= 48) return wide || deep() ? go(RowsShape<3, 2, 64, 3>{}) : go(RowsShape<3, 1, 64, 3>{});
-    if (M <= 64) return wide || deep() ? go(RowsShape<4, 2, 64, 3>{}) : go(RowsShape<4, 1, 64, 3>{});
-    if (M <= 96) return go(RowsShape<6, 2, 64, 3>{});
-    return go(RowsShape<8, 2, 64, 2>{});
+  if (!q8 && tm > 1 && most > 1) {
+    const RowsPlan p = plan(2);
+    if ((long)((N + 127) / 128) * p.nsplit >= 192 && K / p.nsplit >= 1024) return p;
   }
+  return plan(1);
 }
 
 // Measured against the tiled product in K ranges whose partials a row norm adds
@@ -1312,17 +1261,115 @@ bool gemm_rows_takes(int wt, int nt, int M, int K) {
          ((wt == W_BF16 && M <= kRowsMaxBf16) || (wt == W_Q8 && M <= kRowsMaxQ8));
 }
 
+template <int NT, int EPI, bool Q8>
+static hipError_t gemm_rows(const RowsPlan& p, const ActBuf& A, int lda, const void* W, int M,
+                            int N, int K, float* C, size_t c_split, int ldc, const ActBuf& H,
+                            int ldh, float* part, int* sync, int* fault, hipStream_t st,
+                            bool drill) {
+  auto go = [&](auto shape) {
+    using R = decltype(shape);
+    return gemm_rows_launch<NT, R::TM, R::WN, R::KC, R::STG, EPI, Q8>(
+        A, lda, W, M, N, K, p.nsplit, C, c_split, ldc, H, ldh, part, sync, fault, st, drill);
+  };
+  // Slices are 128 deep up to 32 rows and 64 from 33 on (48 rows: gate/up 60.5 us at
+  // 128), the stages as many as leave two workgroups per CU, or one with wide slices.
+  const bool wide = p.wn == 2;
+  if constexpr (Q8) {
+    switch (p.tm) {
+      case 1: return go(RowsShape<1, 1, 128, 4>{});
+      case 2: return wide ? go(RowsShape<2, 2, 128, 3>{}) : go(RowsShape<2, 1, 128, 3>{});
+      case 3: return go(RowsShape<3, 1, 128, 2>{});
+      default: return wide ? go(RowsShape<4, 2, 128, NT <= 2 ? 3 : 2>{}) : go(RowsShape<4, 1, 128, 2>{});
+    }
+  } else {
+    switch (p.tm) {
+      case 1: return wide ? go(RowsShape<1, 2, 128, 3>{}) : go(RowsShape<1, 1, 128, 3>{});
+      case 2: return wide ? go(RowsShape<2, 2, 64, 4>{}) : go(RowsShape<2, 1, 128, 3>{});
+      case 3: return wide ? go(RowsShape<3, 2, 64, 3>{}) : go(RowsShape<3, 1, 64, 3>{});
+      case 4: return wide ? go(RowsShape<4, 2, 64, 3>{}) : go(RowsShape<4, 1, 64, 3>{});
+      case 6: return go(RowsShape<6, 2, 64, 3>{});
+      default: return go(RowsShape<8, 2, 64, 2>{});
+    }
+  }
+}
+
+template <int NT, int EPI>
+static hipError_t gemm_rows_wt(int wt, const RowsPlan& p, const ActBuf& A, int lda, const void* W,
+                               int M, int N, int K, float* C, size_t c_split, int ldc,
+                               const ActBuf& H, int ldh, float* part, int* sync, int* fault,
+                               hipStream_t st, bool drill) {
+  return wt == W_Q8 ? gemm_rows<NT, EPI, true>(p, A, lda, W, M, N, K, C, c_split, ldc, H, ldh, part,
+                                               sync, fault, st, drill)
+                    : gemm_rows<NT, EPI, false>(p, A, lda, W, M, N, K, C, c_split, ldc, H, ldh,
+                                                part, sync, fault, st, drill);
+}
+
+// Split K for products with too few output tiles to fill the chip: as many
+// splits (at most four) as still leave at most two blocks per CU (512), each at least
+// 256 deep.  bf16 weights: or another count, up to eight, that tile_time puts at
+// least 12% below that (8B down at 700 rows 199 us in two ranges, 172 in eight; 32B
+// down at 2048 rows, whose 320 tiles leave 512 places unevenly filled, 1267 us whole
+// and 1037 in four ranges).
+static int tile_split_count(int wt, int nt, int M, int N, int K, int max_split) {
+  if (nt < 1 || M <= 32 || (wt != W_BF16 && wt != W_Q8)) return 1;
+  auto fits = [&](int n) { return K % (2 * kBK * n) == 0 && K / n >= 256; };
+  const int bn = wt == W_BF16 && M >= 1024 ? 256 : 128;
+  const int tiles = ((M + 127) / 128) * ((N + bn - 1) / bn);
+  int n = std::max(1, std::min({max_split, 4, 512 / std::max(tiles, 1)}));
+  while (n > 1 && !fits(n)) --n;
+  if (wt == W_Q8) return n;
+  auto time = [&](int s) { return tile_time(tile_shape(nt, M, N, K, s), nt, M, N, K, s); };
+  int best = n;
+  for (int s = 1; s <= std::min(max_split, 8); ++s)
+    if ((s == 1 || fits(s)) && time(s) < time(best)) best = s;
+  return time(best) < 0.88f * time(n) ? best : n;
+}
+
+int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split) {
+  return gemm_rows_best(wt, nt, M, N, K)
+             ? rows_plan(wt, GEMV_STORE, M, N, K, ~(size_t)0, max_split).nsplit
+             : tile_split_count(wt, nt, M, N, K, max_split);
+}
+
+template <int NT>
+static hipError_t gemm_split_nt(int wt, const ActBuf& A, int lda, const void* W, int M, int N,
+                                int K, int nsplit, float* P, size_t p_split, hipStream_t st) {
+  const ActBuf none{};
+  if (gemm_rows_best(wt, NT, M, N, K)) {
+    const RowsPlan p = rows_plan(wt, GEMV_STORE, M, N, K, ~(size_t)0, nsplit);
+    return p.nsplit == nsplit
+               ? gemm_rows_wt<NT, GEMV_STORE>(wt, p, A, lda, W, M, N, K, P, p_split, N, none, 0,
+                                              nullptr, nullptr, nullptr, st, false)
+               : hipErrorInvalidValue;
+  }
+  if (M <= 32 || K % (2 * kBK * nsplit)) return hipErrorInvalidValue;
+  if (wt == W_Q8)
+    return gemm_q8_launch<NT, GEMV_STORE>(A, lda, W, M, N, K, P, N, none, 0, st, nsplit, p_split);
+  return gemm_dma_pick<NT, GEMV_STORE>(A, lda, W, M, N, K, P, N, none, 0, st, nsplit, p_split);
+}
+
+hipError_t launch_gemm_split(int wt, const ActBuf& A, int lda, const void* W, int M, int N, int K,
+                             int nsplit, float* P, size_t p_split, hipStream_t st) {
+  if (nsplit < 1 || (wt != W_BF16 && wt != W_Q8)) return hipErrorInvalidValue;
+  switch (A.nt) {
+    case 1: return gemm_split_nt<1>(wt, A, lda, W, M, N, K, nsplit, P, p_split, st);
+    case 2: return gemm_split_nt<2>(wt, A, lda, W, M, N, K, nsplit, P, p_split, st);
+    case 3: return gemm_split_nt<3>(wt, A, lda, W, M, N, K, nsplit, P, p_split, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
 hipError_t launch_gemm_rows(int wt, int epi, const ActBuf& A, int lda, const void* W, int M,
                             int N, int K, float* C, int ldc, const ActBuf& H, int ldh,
                             float* part, size_t part_floats, int* sync, int* fault,
                             hipStream_t st, bool drill) {
   if (!gemm_rows_takes(wt, A.nt, M, K))
     return launch_gemm(wt, epi, A, lda, W, M, N, K, C, ldc, H, ldh, st);
-#define WICI_RW(NT_, E)                                                                         \
-  return wt == W_Q8 ? gemm_rows<NT_, E, true>(A, lda, W, M, N, K, C, ldc, H, ldh, part,         \
-                                              part_floats, sync, fault, st, drill)              \
-                    : gemm_rows<NT_, E, false>(A, lda, W, M, N, K, C, ldc, H, ldh, part,        \
-                                               part_floats, sync, fault, st, drill)
+  const bool merge = part && sync && fault;
+  const RowsPlan p = rows_plan(wt, epi, M, N, K, part_floats, merge ? 16 : 1);
+#define WICI_RW(NT_, E)                                                                          \
+  return gemm_rows_wt<NT_, E>(wt, p, A, lda, W, M, N, K, C, 0, ldc, H, ldh, part, sync, fault, st, \
+                              drill)
 #define WICI_RW_NT(E)            \
   switch (A.nt) {                \
     case 1: WICI_RW(1, E);       \

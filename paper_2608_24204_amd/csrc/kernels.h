@@ -210,9 +210,10 @@ bool attn_group_supported(int G);
 hipError_t launch_gemm(int wt, int epi, const ActBuf& A, int lda, const void* W, int M,
                        int N, int K, float* C, int ldc, const ActBuf& H, int ldh,
                        hipStream_t st);
-// The same product (matrix cores, nt >= 1, M > 32) over nsplit K ranges of equal
-// depth (K a multiple of 64 nsplit): range s writes P + s * p_split ([M, N], row
-// stride N, fp32).  gemm_split_count picks nsplit (1: do not split).
+// The same product (matrix cores, nt >= 1) over nsplit K ranges of equal depth: range
+// s writes P + s * p_split ([M, N], row stride N, fp32).  gemm_split_count picks
+// nsplit, at most max_split (1: do not split), for the few-row kernel where that is the
+// best one and for the tiles otherwise.
 hipError_t launch_gemm_split(int wt, const ActBuf& A, int lda, const void* W, int M, int N, int K,
                              int nsplit, float* P, size_t p_split, hipStream_t st);
 int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split);

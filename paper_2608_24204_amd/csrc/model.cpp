@@ -414,8 +414,8 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
   if ((e = wici::launch_embed(wb, m->dw + L.embed, c.vocab, d, m->S<int32_t>(L.tokens) + tok_off,
                               T, nullptr, x, s)))
     return e;
-  // The residual products (O, down) have only d output columns: with few rows
-  // they are split along K into partials that the next row RMSNorm adds to x
+  // The residual products (O, down) have only d output columns: they
+  // are split along K into partials that the next row RMSNorm adds to x
   // (in split order, so the result does not depend on scheduling).
   float* P = m->S<float>(L.kpart);
   const size_t p_split = (size_t)T * d;
@@ -423,20 +423,17 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
   auto room = [&](int n, int most) {
     return (int)std::min<size_t>(most, kMaxKSplit * C * d / ((size_t)T * n));
   };
-  // Few rows: the weight-streaming products, which add their K ranges in the launch
-  // (P holds the partials; a misplaced range is reported through the state).
-  int* gsync = m->S<int>(L.gemm_sync);
-  int* gfault = &reinterpret_cast<DecodeState*>(m->ds + L.state)->fault;
+  // Few rows: the weight-streaming products.  None of a prompt's products adds its K
+  // ranges within the launch, which needs workgroups dealt to the XCDs in turn.
   auto prod = [&](int epi, const wici::ActBuf& in, int K, size_t w, int N, float* out, int ldo,
                   const wici::ActBuf& hout, int ldh) {
     return wici::gemm_rows_best(wb, in.nt, T, N, K)
-               ? wici::launch_gemm_rows(wb, epi, in, K, m->dw + w, T, N, K, out, ldo, hout, ldh, P,
-                                        (size_t)kMaxKSplit * C * d, gsync, gfault, s)
+               ? wici::launch_gemm_rows(wb, epi, in, K, m->dw + w, T, N, K, out, ldo, hout, ldh,
+                                        nullptr, 0, nullptr, nullptr, s)
                : wici::launch_gemm(wb, epi, in, K, m->dw + w, T, N, K, out, ldo, hout, ldh, s);
   };
   auto splits = [&](int terms, int N, int K, int most) {
-    return wici::gemm_rows_best(wb, terms, T, N, K)
-               ? 1 : wici::gemm_split_count(wb, terms, T, N, K, room(N, most));
+    return wici::gemm_split_count(wb, terms, T, N, K, room(N, most));
   };
   const int s_o = splits(rd(att, pl.o).nt, d, qd, kMaxRowSplit);
   const int s_d = splits(rd(h, pl.down).nt, d, F, kMaxRowSplit);

@@ -167,3 +167,38 @@ def test_batch_groups_change_between_steps(cuda_ok):
     finally:
         for m in ms:
             m.close()
+
+
+@pytest.mark.parametrize("weights", ["bf16", "q8"])
+@pytest.mark.parametrize("name", ["narrow", "deep"])
+def test_prompts_have_no_in_launch_sum(cuda_ok, name, weights):
+    """No product of a prompt, whatever its rows, adds its K ranges within the launch
+    (which needs workgroups dealt to the XCDs in turn): with WICI_FLAG_FAULT_DRILL,
+    under which every such sum reports misplaced ranges, prompts succeed and their
+    results are those without the flag, while the batched step fails."""
+    from paper_2608_24204_amd.binding import WICI_E_HIP, WiciError, WiciModel
+    cfg, w, _ = setup(name, weights)
+    toks = np.random.default_rng(6).integers(0, cfg.vocab, 129).astype(np.int32)
+
+    def run(drill):
+        out = []
+        lead = WiciModel(cfg, max_seq=160, fault_drill=drill)
+        ms = [lead]
+        try:
+            lead.load_weights(w)
+            for n in (1, 16, 33, 64, 65, 128, 129):
+                lead.reset_kv()
+                out.append(lead.prefill(toks[:n], want_logits=True))
+            ms.append(WiciModel(cfg, max_seq=160, share_weights_of=lead))
+            ms[1].prefill(toks[:5])
+            if drill:
+                with pytest.raises(WiciError) as e:
+                    lead.decode_batch(ms)
+                assert e.value.status == WICI_E_HIP and "XCD" in str(e.value)
+        finally:
+            for m in ms:
+                m.close()
+        return out
+
+    for (t0, l0), (t1, l1) in zip(run(False), run(True)):
+        assert t0 == t1 and np.array_equal(l0, l1)
