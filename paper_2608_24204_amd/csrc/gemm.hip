@@ -45,7 +45,6 @@ __device__ __forceinline__ void epi_out(float* C, int ldc, const ActBuf& H, int 
 }
 
 // --------------------------------------------------------------------- MFMA
-constexpr int kBK = 32;   // K per step (one v_mfma_f32_16x16x32_bf16 depth)
 constexpr int kLDK = 32;  // LDS row (bf16 elements): 64 bytes, four 16-byte chunks
 
 // LDS position (bf16 elements) of 16-byte chunk `chunk` of tile row `row`: the chunk
@@ -622,11 +621,6 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(const bf16_t* __restrict__ 
 // L1, adds the partials in split order (so the sum does not depend on timing),
 // applies the epilogue and resets the counter.  A split that ran elsewhere
 // sets *fault.
-constexpr int kRowsKC = 128;       // K ranges are multiples of this (whole slices)
-constexpr int kRowsSyncLine = 64;  // ints per tile: counter at 0, XCD records from 32
-constexpr int kRowsMaxTiles = kGemmRowsSyncInts / kRowsSyncLine;  // tiles that can be split
-// Rows the kernel takes.
-constexpr int kRowsMaxBf16 = 128, kRowsMaxQ8 = 64;
 
 // LDS chunk (16 bytes) of a row's chunk c, for rows of CH chunks: rows of 256 bytes
 // all start at bank 0, rows of 128 bytes alternate between two halves.
@@ -1031,55 +1025,6 @@ static hipError_t gemm_dma_launch(const ActBuf& A, int lda, const void* W, int M
   return hipGetLastError();
 }
 
-// Tiles of the bf16 product (four wavefronts each): 128 x 256 (64 x 128 a wavefront:
-// half the activation fragment reads per product), 128 x 128, and 64 x 128 (64 x 32 a
-// wavefront, three stages, three workgroups per CU, for few rows).
-//   Two activation terms, random operands, fp32 output, 128 x 256: 8B gate/up at 1024
-// rows 395 us (1218 TFLOP/s), down in four K ranges 205, gate/up at 2048 rows 751
-// (1281); with fragments read just before their products, and 64-bit addresses in
-// vector registers, the same blocks took 425, 228 and 791.  256 x 256 blocks (eight
-// wavefronts, one workgroup per CU, three stages) measured the same (390, 204, 764),
-// 256 x 128 445, 237 and 839, 256 x 256 on four wavefronts of 128 x 128 562, 264 and
-// 1118; raised wavefront priority around the products 1-4% slower.
-enum TileShape { TILE_128x256 = 0, TILE_128x128 = 1, TILE_64x128 = 2 };
-
-// Time of a product of M x N x K in nsplit K ranges on a tile shape, in us: rounds of
-// resident workgroups times K steps, a step's time depending on how many workgroups
-// share a CU (a lone one waits out its loads; a second and third fill in until the
-// matrix cores are busy) and on the activation terms; plus the partials written and
-// read.  The step times are fitted to 340 measured products of 1B, 8B and 32B shapes
-// at 128 to 2048 rows (7% rms).
-static float tile_time(int shape, int nt, int M, int N, int K, int nsplit) {
-  static const struct { int bm, bn, occ; float t[3][2]; } P[3] = {
-      {128, 256, 2, {{.59f, .18f}, {.36f, .67f}, {0.f, 0.f}}},
-      {128, 128, 2, {{.36f, .13f}, {.34f, .33f}, {0.f, 0.f}}},
-      {64, 128, 3, {{.26f, .05f}, {.49f, .10f}, {.24f, .36f}}}};
-  const auto& p = P[shape];
-  auto step = [&](int k) { return p.t[k - 1][0] + p.t[k - 1][1] * (float)nt; };
-  const long n = (long)((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn) * nsplit;
-  const long rounds = n / (256 * p.occ), rest = n % (256 * p.occ);
-  const float steps = (float)K / (kBK * nsplit);
-  float us = 3.3f + steps * (float)rounds * step(p.occ);
-  if (rest) {
-    const int k = (int)((rest + 255) / 256);
-    const float lo = step(k > 1 ? k - 1 : 1), f = (float)(rest - 256 * (k - 1)) / 256.f;
-    us += steps * (lo + (step(k) - lo) * (0.5f + 0.5f * f));
-  }
-  if (nsplit > 1) us += (float)nsplit * M * N * 1.2e-6f;
-  return us;
-}
-
-// The fastest tile for a split count.  By measurement (us, 128 x 128 against 128 x 256):
-// 8B gate/up 120 and 127 at 200 rows, 191 and 177 at 333, 255 and 203 at 512, 366
-// and 295 at 700; O in four ranges 44 and 46 at 512; 64 x 128 takes 17 for O in four
-// ranges at 128 rows against 26 and 36.
-static int tile_shape(int nt, int M, int N, int K, int nsplit) {
-  int best = 0;
-  for (int s = 1; s < 3; ++s)
-    if (tile_time(s, nt, M, N, K, nsplit) < tile_time(best, nt, M, N, K, nsplit)) best = s;
-  return best;
-}
-
 template <int NT, int EPI>
 static hipError_t gemm_dma_pick(const ActBuf& A, int lda, const void* W, int M, int N, int K,
                                 float* C, int ldc, const ActBuf& H, int ldh, hipStream_t st,
@@ -1193,73 +1138,12 @@ static hipError_t gemm_f32(const ActBuf& A, int lda, const WT* W, int M, int N, 
   return hipGetLastError();
 }
 
-// Splits along K for the few-rows kernel: the fewest (up to `most`) that give at
-// least 192 workgroups of bn weight rows with whole 128-deep slices, as far as the
-// partials (tm 16-row tiles) fit `part_floats` and the tiles the sync lines.
-// (Measured at 16 rows on the 8B shapes, bf16: QKV 2 splits 12.6 us, 4 13.3; O 4
-// splits 9.9 us, 8 10.3; down 4 splits 24.8 us, 7 27.3; at 48 rows QKV 2 splits
-// 19.1 us, 8 20.0: more, shorter workgroups pay more in pipeline fill and in the
-// sum.)
-static int gemm_rows_splits(int tm, int bn, int N, int K, size_t part_floats, int most) {
-  const int T = (N + bn - 1) / bn;
-  if (T > kRowsMaxTiles) return 1;
-  int best = 1;
-  for (int s = 2; s <= most && T * best < 192; ++s) {
-    if (K % (s * kRowsKC)) continue;
-    if ((size_t)T * s * bn * 16 * tm > part_floats) break;
-    best = s;
-  }
-  return best;
-}
-
 // The launch shapes of the few-rows kernel: TM 16-row tiles, 64 WN weight rows per
 // workgroup, KC-deep slices in STG stages.
 template <int TM_, int WN_, int KC_, int STG_>
 struct RowsShape {
   static constexpr int TM = TM_, WN = WN_, KC = KC_, STG = STG_;
 };
-
-// 16-row tiles, 64-row column tiles per workgroup and K ranges of the few-rows kernel.
-struct RowsPlan {
-  int tm, wn, nsplit;
-};
-
-static RowsPlan rows_plan(int wt, int epi, int M, int N, int K, size_t part_floats, int most) {
-  const bool q8 = wt == W_Q8;
-  const int tm = M <= 64 ? (M + 15) / 16 : M <= 96 ? 6 : 8;
-  auto plan = [&](int wn) {
-    return RowsPlan{tm, wn, gemm_rows_splits(tm, 64 * wn, N, K, part_floats, most)};
-  };
-  if (tm > 4) return plan(2);
-  // 128 weight rows per workgroup (each activation fragment read for twice the
-  // columns) where that alone still gives 192 workgroups: 8B gate/up, bf16, 43.2 ->
-  // 40.2 us at 16 rows, 49.2 -> 42.7 at 32, 55.5 -> 47.4 at 48, 62.3 -> 55.1 at 64;
-  // Q8 43.8 -> 39.6 at 32 and 78 -> 66 at 64, but 31.8 -> 33.3 at 8 and 47.8 -> 49.5
-  // at 48.  Narrower products keep 64 (O at 48 rows 15.6 against 17.9 us).
-  if (epi != GEMV_RESID && N >= 192 * 128 && !(q8 && (tm == 1 || tm == 3))) return plan(2);
-  // Also, from 17 rows of bf16 weights, where the K ranges that give 192 workgroups are
-  // still 1024 deep: QKV 19.4 -> 16.4 us at 32 rows, 23.1 -> 20.0 at 48, 27.1 -> 23.2 at
-  // 64, down 27.4 -> 26.6, 33.1 -> 29.0 and 37.3 -> 32.8 (at 16 rows 25.2 against 25.3; O,
-  // whose ranges would be 512 deep, 16.5 -> 22.0 at 48).
-  if (!q8 && tm > 1 && most > 1) {
-    const RowsPlan p = plan(2);
-    if ((long)((N + 127) / 128) * p.nsplit >= 192 && K / p.nsplit >= 1024) return p;
-  }
-  return plan(1);
-}
-
-// Measured against the tiled product in K ranges whose partials a row norm adds
-// anyway (us, two terms): O 20 against 17 at 64 rows and 30 against 17 at 96, down 43
-// against 50 and 54 against 50; but 8B gate/up 78 against 97 at 96 rows, 95 against 97
-// at 128.
-bool gemm_rows_best(int wt, int nt, int M, int N, int K) {
-  return gemm_rows_takes(wt, nt, M, K) && (M <= 64 || N >= 192 * 128);
-}
-
-bool gemm_rows_takes(int wt, int nt, int M, int K) {
-  return nt >= 1 && nt <= 3 && M >= 1 && K % kRowsKC == 0 &&
-         ((wt == W_BF16 && M <= kRowsMaxBf16) || (wt == W_Q8 && M <= kRowsMaxQ8));
-}
 
 template <int NT, int EPI, bool Q8>
 static hipError_t gemm_rows(const RowsPlan& p, const ActBuf& A, int lda, const void* W, int M,
@@ -1304,38 +1188,11 @@ static hipError_t gemm_rows_wt(int wt, const RowsPlan& p, const ActBuf& A, int l
                                                 part, sync, fault, st, drill);
 }
 
-// Split K for products with too few output tiles to fill the chip: as many
-// splits (at most four) as still leave at most two blocks per CU (512), each at least
-// 256 deep.  bf16 weights: or another count, up to eight, that tile_time puts at
-// least 12% below that (8B down at 700 rows 199 us in two ranges, 172 in eight; 32B
-// down at 2048 rows, whose 320 tiles leave 512 places unevenly filled, 1267 us whole
-// and 1037 in four ranges).
-static int tile_split_count(int wt, int nt, int M, int N, int K, int max_split) {
-  if (nt < 1 || M <= 32 || (wt != W_BF16 && wt != W_Q8)) return 1;
-  auto fits = [&](int n) { return K % (2 * kBK * n) == 0 && K / n >= 256; };
-  const int bn = wt == W_BF16 && M >= 1024 ? 256 : 128;
-  const int tiles = ((M + 127) / 128) * ((N + bn - 1) / bn);
-  int n = std::max(1, std::min({max_split, 4, 512 / std::max(tiles, 1)}));
-  while (n > 1 && !fits(n)) --n;
-  if (wt == W_Q8) return n;
-  auto time = [&](int s) { return tile_time(tile_shape(nt, M, N, K, s), nt, M, N, K, s); };
-  int best = n;
-  for (int s = 1; s <= std::min(max_split, 8); ++s)
-    if ((s == 1 || fits(s)) && time(s) < time(best)) best = s;
-  return time(best) < 0.88f * time(n) ? best : n;
-}
-
-int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split) {
-  return gemm_rows_best(wt, nt, M, N, K)
-             ? rows_plan(wt, GEMV_STORE, M, N, K, ~(size_t)0, max_split).nsplit
-             : tile_split_count(wt, nt, M, N, K, max_split);
-}
-
 template <int NT>
 static hipError_t gemm_split_nt(int wt, const ActBuf& A, int lda, const void* W, int M, int N,
                                 int K, int nsplit, float* P, size_t p_split, hipStream_t st) {
   const ActBuf none{};
-  if (gemm_rows_best(wt, NT, M, N, K)) {
+  if (gemm_rows_best(wt, NT, M, N, K, nsplit)) {
     const RowsPlan p = rows_plan(wt, GEMV_STORE, M, N, K, ~(size_t)0, nsplit);
     return p.nsplit == nsplit
                ? gemm_rows_wt<NT, GEMV_STORE>(wt, p, A, lda, W, M, N, K, P, p_split, N, none, 0,

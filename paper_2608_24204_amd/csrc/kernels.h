@@ -4,15 +4,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_plan.h"
+
 namespace wici {
 
-enum GemvEpi { GEMV_STORE = 0, GEMV_RESID = 1, GEMV_SWIGLU = 2, GEMV_ARGMAX = 3, GEMV_QKV = 4 };
-
-// Weight storage (the values of the C ABI's wici_dtype).  A W_Q8 matrix [N, K]
-// is N*K code bytes (q + 128, row-major) followed, at the next 256-byte
-// boundary, by N*K/32 half-precision block scales (row-major, one per 32
-// consecutive weights of a row); the weight is (code - 128) * scale.
-enum WType { W_F32 = 0, W_BF16 = 1, W_Q8 = 2 };
 __host__ __device__ inline size_t q8_scale_offset(size_t n, size_t k) {
   return (n * k + 255) / 256 * 256;
 }
@@ -212,11 +207,9 @@ hipError_t launch_gemm(int wt, int epi, const ActBuf& A, int lda, const void* W,
                        hipStream_t st);
 // The same product (matrix cores, nt >= 1) over nsplit K ranges of equal depth: range
 // s writes P + s * p_split ([M, N], row stride N, fp32).  gemm_split_count picks
-// nsplit, at most max_split (1: do not split), for the few-row kernel where that is the
-// best one and for the tiles otherwise.
+// nsplit.
 hipError_t launch_gemm_split(int wt, const ActBuf& A, int lda, const void* W, int M, int N, int K,
                              int nsplit, float* P, size_t p_split, hipStream_t st);
-int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split);
 // The product for few rows (a batched decode step, a short prompt): bf16 or Q8
 // weights, nt >= 1, K a multiple of 128, as many rows as gemm_rows_takes says,
 // staged through LDS in whole lines; otherwise launch_gemm.  With part (part_floats
@@ -226,10 +219,6 @@ int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split);
 // splits of a tile on one XCD; *fault is set to 1 if they were not (the result
 // cannot be trusted then; with drill, every split-K sum reports so, for tests of
 // the error path).  Launches that share sync must not overlap.
-constexpr int kGemmRowsSyncInts = 512 * 64;
-bool gemm_rows_takes(int wt, int nt, int M, int K);
-// Whether that beats the tiled product split along K (launch_gemm_split).
-bool gemm_rows_best(int wt, int nt, int M, int N, int K);
 hipError_t launch_gemm_rows(int wt, int epi, const ActBuf& A, int lda, const void* W, int M,
                             int N, int K, float* C, int ldc, const ActBuf& H, int ldh,
                             float* part, size_t part_floats, int* sync, int* fault,

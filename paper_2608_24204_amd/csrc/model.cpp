@@ -427,7 +427,7 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
   // ranges within the launch, which needs workgroups dealt to the XCDs in turn.
   auto prod = [&](int epi, const wici::ActBuf& in, int K, size_t w, int N, float* out, int ldo,
                   const wici::ActBuf& hout, int ldh) {
-    return wici::gemm_rows_best(wb, in.nt, T, N, K)
+    return wici::gemm_rows_best(wb, in.nt, T, N, K, 1)
                ? wici::launch_gemm_rows(wb, epi, in, K, m->dw + w, T, N, K, out, ldo, hout, ldh,
                                         nullptr, 0, nullptr, nullptr, s)
                : wici::launch_gemm(wb, epi, in, K, m->dw + w, T, N, K, out, ldo, hout, ldh, s);
@@ -539,21 +539,22 @@ hipError_t enqueue_decode_batch(wici_model* m, int B) {
   int* gfault = &reinterpret_cast<DecodeState*>(m->ds + L.state)->fault;
   auto prod = [&](int epi, const wici::ActBuf& in, int K, size_t w, int N, float* out, int ldo,
                   const wici::ActBuf& hout, int ldh) {
-    return wici::launch_gemm_rows(wb, epi, in, K, m->dw + w, B, N, K, out, ldo, hout, ldh,
-                                  gpart, gpart_floats, gsync, gfault, s,
-                                  (c.flags & WICI_FLAG_FAULT_DRILL) != 0);
+    return wici::gemm_rows_merge_best(wb, in.nt, B, N, K)
+               ? wici::launch_gemm_rows(wb, epi, in, K, m->dw + w, B, N, K, out, ldo, hout, ldh,
+                                        gpart, gpart_floats, gsync, gfault, s,
+                                        (c.flags & WICI_FLAG_FAULT_DRILL) != 0)
+               : wici::launch_gemm(wb, epi, in, K, m->dw + w, B, N, K, out, ldo, hout, ldh, s);
   };
 #define WICI_TRY(call) \
   do {                 \
     if ((e = (call))) return e; \
   } while (0)
-  // the residual products: from the row count where that is faster, tiled in K ranges
-  // whose partials the next row norm adds (as in a prefill chunk)
+  // the residual products: K ranges whose partials the next row norm adds (as in a
+  // prefill chunk)
   const size_t p_split = (size_t)B * d;
   auto splits = [&](const wici::ActBuf& in, int K) {
-    return wici::gemm_rows_best(wb, in.nt, B, d, K)
-               ? 1 : wici::gemm_split_count(wb, in.nt, B, d, K,
-                                            (int)std::min<size_t>(kMaxRowSplit, kMaxKSplit * C / B));
+    return wici::gemm_split_count(wb, in.nt, B, d, K,
+                                  (int)std::min<size_t>(kMaxRowSplit, kMaxKSplit * C / B));
   };
   const int s_o = splits(rd(att, pl.o), qd), s_d = splits(rd(h, pl.down), F);
   auto resid = [&](const wici::ActBuf& in, int K, size_t w, int nsplit) {

@@ -19,12 +19,15 @@ pytestmark = pytest.mark.gpu
 
 # narrow: every product split along K (3 and 9 ranges of 128 among them), vocab and
 # QKV rows no multiple of a tile; wide: gate/up and LM head past 192 x 128 rows, the
-# LM head's last tile ragged; deep: the down product in K ranges of 1024 on 128 weight rows
+# LM head's last tile ragged; deep: the down product in K ranges of 1024 on 128 weight rows;
+# mid: gate/up and LM head of 128 to 192 x 128 rows, which leave the few-row kernel past 64 rows
 CFGS = {
     "narrow": configs.ModelConfig(name="t_rows", key=110, n_layers=2, d_model=384, n_heads=4,
                                   n_kv_heads=2, head_dim=64, ffn_dim=1152, vocab=1003),
     "wide": configs.ModelConfig(name="t_rows_wide", key=111, n_layers=2, d_model=256, n_heads=2,
                                 n_kv_heads=1, head_dim=128, ffn_dim=12416, vocab=24601),
+    "mid": configs.ModelConfig(name="t_rows_mid", key=113, n_layers=1, d_model=256, n_heads=2,
+                               n_kv_heads=1, head_dim=128, ffn_dim=8320, vocab=17001),
     "deep": configs.ModelConfig(name="t_rows_deep", key=112, n_layers=1, d_model=2048, n_heads=4,
                                 n_kv_heads=1, head_dim=128, ffn_dim=12288, vocab=1003),
 }
@@ -97,7 +100,8 @@ def test_long_prompts_match_oracle(cuda_ok, name, sizes, weights):
 
 @pytest.mark.parametrize("weights", ["bf16", "q8"])
 @pytest.mark.parametrize("name,n", [("narrow", 9), ("narrow", 17), ("narrow", 48), ("narrow", 64),
-                                    ("narrow", 65), ("narrow", 130), ("wide", 3), ("wide", 49)])
+                                    ("narrow", 65), ("narrow", 130), ("wide", 3), ("wide", 49), ("wide", 97),
+                                    ("mid", 64), ("mid", 65), ("mid", 128)])
 def test_batches_match_oracle(cuda_ok, name, weights, n):
     """Batched steps with given tokens, sequences of different lengths."""
     from paper_2608_24204_amd.binding import WiciModel

@@ -1,0 +1,75 @@
+"""Which kernel a matrix product runs on: the rules of csrc/gemm_plan.h, evaluated on
+the CPU."""
+
+from __future__ import annotations
+
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+GXX = shutil.which("g++")
+BF16, Q8 = 1, 2
+
+pytestmark = pytest.mark.skipif(GXX is None, reason="g++ not available")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    """Answers (tuples of ints) to a list of questions (see the harness)."""
+    exe = str(tmp_path_factory.mktemp("plan") / "plan")
+    subprocess.run([GXX, "-O1", "-std=c++17", "-Wall", "-Werror", "-I",
+                    os.path.join(ROOT, "paper_2608_24204_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "native", "plan_harness.cpp"), "-o", exe], check=True)
+
+    def run(questions):
+        text = "".join(" ".join(map(str, q)) + "\n" for q in questions)
+        r = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, timeout=60)
+        out = [tuple(map(int, l.split())) for l in r.stdout.splitlines()]
+        assert len(out) == len(questions)
+        return out
+
+    return run
+
+
+def test_ranges_are_whole_and_the_launch_agrees(ask):
+    """Over random shapes: K ranges of whole steps, no more than asked for, and a launch
+    that is given the count picks the kernel that the count was made for."""
+    rng = np.random.default_rng(0)
+    qs = []
+    for _ in range(20000):
+        wt, nt = int(rng.choice([BF16, Q8])), int(rng.integers(1, 4))
+        M = int(np.exp(rng.uniform(0, np.log(8192))))
+        N = 64 * int(np.exp(rng.uniform(0, np.log(900)))) + int(rng.choice([0, 0, 1, 37]))
+        K = 64 * int(np.exp(rng.uniform(0, np.log(512))))
+        qs.append(("ranges", wt, nt, M, N, K, int(rng.integers(1, 9))))
+    for q, (n, rows, rows_n) in zip(qs, ask(qs)):
+        _, wt, nt, M, N, K, most = q
+        assert 1 <= n <= most, q
+        assert rows == rows_n, q
+        if n > 1:
+            assert K % (n * (128 if rows else 64)) == 0, q
+    split = [(q, n) for q, (n, rows, _) in zip(qs, ask(qs)) if rows]
+    got = ask([("rows",) + q[1:6] + (n,) for q, n in split])
+    assert all(p[2] == n for p, (_, n) in zip(got, split))
+
+
+@pytest.mark.parametrize("M,N,K,most,rows", [
+    (64, 4096, 4096, 8, True), (96, 4096, 14336, 8, True), (96, 6144, 4096, 4, True),
+    (96, 28672, 4096, 1, True), (128, 28672, 4096, 1, True), (96, 5120, 27648, 8, True),
+    (128, 4096, 4096, 8, False), (128, 6144, 4096, 4, False), (96, 2048, 8192, 8, False),
+    (96, 55296, 5120, 1, False), (128, 55296, 5120, 1, False), (129, 28672, 4096, 1, False)])
+def test_prompts_leave_the_few_row_kernel_where_tiles_are_faster(ask, M, N, K, most, rows):
+    """Either side of the lines whose measured times stand beside the rule."""
+    assert ask([("ranges", BF16, 2, M, N, K, most)])[0][1] == rows
+
+
+@pytest.mark.parametrize("M,N,K,rows", [
+    (64, 128256, 4096, True), (65, 128256, 4096, False), (128, 152064, 5120, False),
+    (80, 55296, 5120, False), (128, 28672, 4096, True), (80, 16384, 2048, False),
+    (128, 6144, 4096, True), (128, 3072, 2048, True), (129, 6144, 4096, False)])
+def test_batches_leave_the_few_row_kernel_where_tiles_are_faster(ask, M, N, K, rows):
+    assert ask([("merge", BF16, 3, M, N, K, 0)])[0][0] == rows
