@@ -1029,7 +1029,7 @@ template <int NT, int EPI>
 static hipError_t gemm_dma_pick(const ActBuf& A, int lda, const void* W, int M, int N, int K,
                                 float* C, int ldc, const ActBuf& H, int ldh, hipStream_t st,
                                 int nsplit = 1, size_t c_split = 0) {
-  switch (tile_shape(NT, M, N, K, nsplit)) {
+  switch (tile_shape(NT, M, N, K, nsplit, EPI == GEMV_SWIGLU)) {
     case TILE_128x256:
       return gemm_dma_launch<NT, EPI, 2, 2, 4, 8, 2, 1, true>(A, lda, W, M, N, K, C, ldc, H, ldh,
                                                               st, nsplit, c_split);
@@ -1037,7 +1037,7 @@ static hipError_t gemm_dma_pick(const ActBuf& A, int lda, const void* W, int M, 
       return gemm_dma_launch<NT, EPI, 2, 2, 4, 4, 2, 2, false>(A, lda, W, M, N, K, C, ldc, H, ldh,
                                                                st, nsplit, c_split);
     default:
-      // (SwiGLU's dealt columns need four tiles a wavefront: two wavefronts of 64 x 64)
+      // (SwiGLU's dealt columns need four tiles a wavefront: 2 x 2 of 32 x 64)
       if constexpr (EPI == GEMV_SWIGLU)
         return gemm_dma_launch<NT, EPI, 2, 2, 2, 4, 3, NT % 2 ? 1 : 2, true>(
             A, lda, W, M, N, K, C, ldc, H, ldh, st, nsplit, c_split);

@@ -20,7 +20,7 @@ constexpr int kBK = 32;   // K per step (one v_mfma_f32_16x16x32_bf16 depth)
 // ---- tiles
 // Tiles of the bf16 product (four wavefronts each): 128 x 256 (64 x 128 a wavefront:
 // half the activation fragment reads per product), 128 x 128, and 64 x 128 (64 x 32 a
-// wavefront, three stages, three workgroups per CU, for few rows).
+// wavefront, three stages, for few rows).
 //   Two activation terms, random operands, fp32 output, 128 x 256: 8B gate/up at 1024
 // rows 395 us (1218 TFLOP/s), down in four K ranges 205, gate/up at 2048 rows 751
 // (1281); with fragments read just before their products, and 64-bit addresses in
@@ -29,50 +29,78 @@ constexpr int kBK = 32;   // K per step (one v_mfma_f32_16x16x32_bf16 depth)
 // 256 x 128 445, 237 and 839, 256 x 256 on four wavefronts of 128 x 128 562, 264 and
 // 1118; raised wavefront priority around the products 1-4% slower.
 enum TileShape { TILE_128x256 = 0, TILE_128x128 = 1, TILE_64x128 = 2 };
+constexpr int kTileShapes = 3;
 
-// Time of a product of M x N x K in nsplit K ranges on a tile shape, in us: rounds of
-// resident workgroups times K steps, a step's time depending on how many workgroups
-// share a CU (a lone one waits out its loads; a second and third fill in until the
-// matrix cores are busy) and on the activation terms; plus the partials written and
-// read.  The step times are fitted to 340 measured products of 1B, 8B and 32B shapes
-// at 128 to 2048 rows (7% rms).
-inline float tile_time(int shape, int nt, int M, int N, int K, int nsplit) {
-  static const struct { int bm, bn, occ; float t[3][2]; } P[3] = {
-      {128, 256, 2, {{.59f, .18f}, {.36f, .67f}, {0.f, 0.f}}},
-      {128, 128, 2, {{.36f, .13f}, {.34f, .33f}, {0.f, 0.f}}},
-      {64, 128, 3, {{.26f, .05f}, {.49f, .10f}, {.24f, .36f}}}};
-  const auto& p = P[shape];
-  auto step = [&](int k) { return p.t[k - 1][0] + p.t[k - 1][1] * (float)nt; };
-  const long n = (long)((M + p.bm - 1) / p.bm) * ((N + p.bn - 1) / p.bn) * nsplit;
-  const long rounds = n / (256 * p.occ), rest = n % (256 * p.occ);
-  const float steps = (float)K / (kBK * nsplit);
-  float us = 3.3f + steps * (float)rounds * step(p.occ);
+// Per shape and 1, 2 or 3 activation terms: workgroups that fit on a CU (by LDS, 64 bytes
+// a row, term and stage, and by registers); the time of a K step, us, with 1, 2, ... of
+// them on the CU (a lone one waits out its loads; more fill in until the matrix cores are
+// busy); and the time a MB takes to reach an XCD's L2.  Fitted to the products of
+// profiles/tile_times.csv (4761: 1B, 8B, 32B and smaller shapes, 65 to 4096 rows, 1
+// to 8 K ranges): 8% rms.  The two wavefront layouts of 64 x 128 are rows of their own.
+struct Tile {
+  int bm, bn;
+  bool by_columns;  // an XCD owns column tiles (otherwise a run of tiles, row by row)
+  int fit[3];
+  float step[3][4], fetch[3];
+};
+inline const Tile& tile_of(int shape, bool swiglu) {
+  static const Tile T[kTileShapes + 1] = {
+      {128, 256, true, {2, 2, 2}, {{.62f, 1.04f}, {.82f, 1.37f}, {1.05f, 2.13f}}, {.64f, .56f, .65f}},
+      {128, 128, false, {4, 3, 2}, {{.43f, .60f, .88f, 1.25f}, {.55f, .89f, 1.40f}, {.67f, 1.24f}},
+       {.28f, .29f, .41f}},
+      {64, 128, true, {4, 3, 2}, {{.30f, .45f, .70f, .89f}, {.32f, .65f, .96f}, {.37f, .80f}},
+       {.25f, .17f, .30f}},
+      {64, 128, true, {4, 3, 2}, {{.26f, .44f, .71f, .82f}, {.33f, .64f, .95f}, {.38f, .84f}},
+       {.63f, .19f, .19f}}};
+  return T[shape == TILE_64x128 && swiglu ? kTileShapes : shape];
+}
+
+// Time of a product of M x N x K in nsplit K ranges, us: on the XCD with most workgroups
+// (32 CUs; tiles that do not divide into eight leave some XCDs less), rounds of resident
+// ones times K steps, plus the rows and columns that it reads through its L2, plus the
+// partials written.
+inline float tile_time(int shape, bool swiglu, int nt, int M, int N, int K, int nsplit) {
+  const Tile& t = tile_of(shape, swiglu);
+  const int fit = t.fit[nt - 1], places = 32 * fit;
+  const int rows = (M + t.bm - 1) / t.bm, cols = (N + t.bn - 1) / t.bn;
+  const int own = t.by_columns ? (cols + 7) / 8 * rows : (rows * cols + 7) / 8;  // a range's
+  const int n = own * nsplit, rest = n % places;
+  const float* step = t.step[nt - 1];
+  float per_step = (float)(n / places) * step[fit - 1];
   if (rest) {
-    const int k = (int)((rest + 255) / 256);
-    const float lo = step(k > 1 ? k - 1 : 1), f = (float)(rest - 256 * (k - 1)) / 256.f;
-    us += steps * (lo + (step(k) - lo) * (0.5f + 0.5f * f));
+    const int k = (rest + 31) / 32;
+    const float lo = step[k > 1 ? k - 2 : 0], f = (float)(rest - 32 * (k - 1)) / 32.f;
+    per_step += lo + (step[k - 1] - lo) * (0.5f + 0.5f * f);
   }
-  if (nsplit > 1) us += (float)nsplit * M * N * 1.2e-6f;
+  // tiles at work together, and what they read
+  const int now = std::min(places, own), line = t.by_columns ? rows : cols;
+  const int lines = (now + line - 1) / line, across = std::min(line, now);
+  const int r = t.by_columns ? across : lines, c = t.by_columns ? lines : across;
+  const float mb = (float)(r * t.bm * nt + c * t.bn) * 64e-6f * (float)(K / kBK) *
+                   std::max(1.f, (float)own / (float)places);
+  float us = 3.3f + per_step * (float)K / (float)(kBK * nsplit) + mb * t.fetch[nt - 1];
+  if (nsplit > 1) us += (float)nsplit * M * N * 0.5e-6f;
   return us;
 }
 
-// The fastest tile for a split count.  By measurement (us, 128 x 128 against 128 x 256):
-// 8B gate/up 120 and 127 at 200 rows, 191 and 177 at 333, 255 and 203 at 512, 366
-// and 295 at 700; O in four ranges 44 and 46 at 512; 64 x 128 takes 17 for O in four
-// ranges at 128 rows against 26 and 36.
-inline int tile_shape(int nt, int M, int N, int K, int nsplit) {
+// The fastest tile for a split count.
+inline int tile_shape(int nt, int M, int N, int K, int nsplit, bool swiglu) {
   int best = 0;
-  for (int s = 1; s < 3; ++s)
-    if (tile_time(s, nt, M, N, K, nsplit) < tile_time(best, nt, M, N, K, nsplit)) best = s;
+  for (int s = 1; s < kTileShapes; ++s)
+    if (tile_time(s, swiglu, nt, M, N, K, nsplit) < tile_time(best, swiglu, nt, M, N, K, nsplit))
+      best = s;
   return best;
 }
 
-// Split K for products with too few output tiles to fill the chip: as many
-// splits (at most four) as still leave at most two blocks per CU (512), each at least
-// 256 deep.  bf16 weights: or another count, up to eight, that tile_time puts at
-// least 12% below that (8B down at 700 rows 199 us in two ranges, 172 in eight; 32B
-// down at 2048 rows, whose 320 tiles leave 512 places unevenly filled, 1267 us whole
-// and 1037 in four ranges).
+// K ranges of a tiled product whose partials another kernel adds, each at least 256 deep:
+// as many (at most four) as still leave at most two blocks per CU (512).  bf16 weights: or
+// up to eight, if the time with the partials' reading is at least 8% below that count's;
+// or fewer for a fifth, since longer fp32 sums are less exact (1B with an fp32 cache, logits
+// from 64 bits 3.0e-6; QKV and O at 512 rows in one and two ranges instead of four 4.1e-6).
+// Over the measured products of more than 128 rows count and tile then cost 4.2% more than
+// the best ones on average, the worst choice 39% (1B down, one term, 4096 rows): 32B O at
+// 333 rows 51.9 us, 74.3 on the wider tile; 32B down at 1024 rows 552 in eight ranges, 707
+// in three, at 2048 rows 1035 in four, 1197 in two.
 inline int tile_split_count(int wt, int nt, int M, int N, int K, int max_split) {
   if (nt < 1 || M <= 32 || (wt != W_BF16 && wt != W_Q8)) return 1;
   auto fits = [&](int n) { return K % (2 * kBK * n) == 0 && K / n >= 256; };
@@ -81,11 +109,17 @@ inline int tile_split_count(int wt, int nt, int M, int N, int K, int max_split) 
   int n = std::max(1, std::min({max_split, 4, 512 / std::max(tiles, 1)}));
   while (n > 1 && !fits(n)) --n;
   if (wt == W_Q8) return n;
-  auto time = [&](int s) { return tile_time(tile_shape(nt, M, N, K, s), nt, M, N, K, s); };
+  auto time = [&](int s) {
+    return tile_time(tile_shape(nt, M, N, K, s, false), false, nt, M, N, K, s) +
+           (s > 1 ? (float)s * M * N * 0.7e-6f : 0.f);
+  };
+  const float usual = time(n);
   int best = n;
   for (int s = 1; s <= std::min(max_split, 8); ++s)
-    if ((s == 1 || fits(s)) && time(s) < time(best)) best = s;
-  return time(best) < 0.88f * time(n) ? best : n;
+    if (s != n && (s == 1 || fits(s)) && time(s) < (s < n ? 0.8f : 0.92f) * usual &&
+        time(s) < time(best))
+      best = s;
+  return best;
 }
 
 // ---- few rows
