@@ -12,6 +12,8 @@ import subprocess
 import numpy as np
 import pytest
 
+from tests.test_gpu_rows import CFGS
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 GXX = shutil.which("g++")
 BF16, Q8 = 1, 2
@@ -133,3 +135,30 @@ def test_chosen_tiles_and_ranges_are_near_the_best_measured(ask, measured):
             loss.append(by[k][n, s] / min(by[k].values()))
     assert len(loss) > 0.9 * len(keys)
     assert np.mean(loss) <= 1.045 and np.max(loss) <= 1.40, (np.mean(loss), np.max(loss))
+
+
+def prompt_products(ask, cfg, M, chunk=2048):
+    """(kernel, ranges, N, K) of the four products of a prompt of M rows: the rules as the
+    prefill applies them, with the default mode's activation terms (3, 2, 2, 2)."""
+    d, F, qd = cfg.d_model, cfg.ffn_dim, cfg.n_heads * cfg.head_dim
+    out = {}
+    for name, nt, N, K, most in (("qkv", 3, qd + 2 * cfg.n_kv_heads * cfg.head_dim, d, 4),
+                                 ("o", 2, d, qd, 8), ("gu", 2, 2 * F, d, 1), ("down", 2, d, F, 8)):
+        most = min(most, 4 * chunk * d // (M * N)) if name != "gu" else 1
+        n, rows, _ = ask([("ranges", BF16, nt, M, N, K, max(most, 1))])[0]
+        n = n if name != "gu" else 1
+        if rows or M <= 32:
+            out[name] = ("rows" if rows else "skinny", n, N, K)
+        else:
+            s = ask([(kind(name == "gu"), BF16, nt, M, N, K, n)])[0][0]
+            out[name] = (TILES[s], n, N, K)
+    return out
+
+
+def test_odd_depths_reach_the_other_kernels(ask):
+    """K of 64 mod 128: k_gemm_skinny up to 32 rows, tiles from 33."""
+    for name in ("odd", "step"):
+        for M, want in ((1, "skinny"), (32, "skinny"), (33, "64x128"), (129, "64x128")):
+            got = prompt_products(ask, CFGS[name], M)
+            assert {v[0] for v in got.values()} == {want}, (name, M, got)
+            assert all(v[3] // v[1] % 128 == 64 for v in got.values())
