@@ -38,9 +38,22 @@ CFGS = {
                                 n_kv_heads=1, head_dim=64, ffn_dim=64, vocab=251),
 }
 
+# Every tile with every epilogue at row and column remainders (test_product_plan.py checks
+# that these are what the rules choose for these rows): cols for stored and SwiGLU products,
+# resid for the residual ones, ranges for K ranges.
+TILE_ROWS = {"cols": [200, 333, 600, 1000], "resid": [333, 600, 1000], "ranges": [100, 333, 777]}
+TILE_CFGS = {
+    "cols": configs.ModelConfig(name="t_cols", key=116, n_layers=2, d_model=1088, n_heads=85,
+                                n_kv_heads=17, head_dim=64, ffn_dim=4160, vocab=1003),
+    "resid": configs.ModelConfig(name="t_resid", key=117, n_layers=2, d_model=6208, n_heads=20,
+                                 n_kv_heads=4, head_dim=128, ffn_dim=1472, vocab=1003),
+    "ranges": configs.ModelConfig(name="t_ranges", key=118, n_layers=2, d_model=4032, n_heads=32,
+                                  n_kv_heads=4, head_dim=128, ffn_dim=512, vocab=1003),
+}
+
 
 def setup(name, weights):
-    cfg = CFGS[name].with_(weight_dtype=weights)
+    cfg = {**CFGS, **TILE_CFGS}[name].with_(weight_dtype=weights)
     w = inputs.make_weights(cfg, gain_std=0.1)
     return cfg, w, (q8_model_f64(w) if weights == "q8" else inputs.weights_f64(cfg, w))
 
@@ -83,9 +96,8 @@ def test_short_prompts_match_oracle(cuda_ok, name, weights):
 @pytest.mark.parametrize("name,sizes", [("narrow", [200, 257, 500, 640, 1023, 1024, 1281]),
                                         ("wide", [130, 200, 257, 400])])
 def test_long_prompts_match_oracle(cuda_ok, name, sizes, weights):
-    """130 to 1281 rows: the tiled products with ragged row and column tiles (384, 512
-    and 2304 columns against tiles of 128 and 256; 24832 for the wide ones), split
-    along K and not, on every tile shape."""
+    """130 to 1281 rows: the tiled products with ragged rows, whole column tiles (384, 512,
+    2304 and 24832 columns), split along K and not."""
     from paper_2608_24204_amd.binding import WiciModel
     cfg, w, w64 = setup(name, weights)
     toks = np.random.default_rng(4).integers(0, cfg.vocab, sizes[-1]).astype(np.int32)
@@ -98,6 +110,29 @@ def test_long_prompts_match_oracle(cuda_ok, name, sizes, weights):
             m.reset_kv()
             tok, lg = m.prefill(toks[:n], want_logits=True)
             print(f"[rows] {name} {weights} {n} rows: {inf_rel(lg, ref[n - 1]):.2e}", flush=True)
+            assert inf_rel(lg, ref[n - 1]) <= 1e-3, n
+            check_kv(m, orc, n)
+    finally:
+        m.close()
+
+
+@pytest.mark.parametrize("name", list(TILE_CFGS))
+def test_ragged_tiles_match_oracle(cuda_ok, name):
+    """Every tile with every epilogue, rows and columns no multiple of it: the second
+    layer's keys and values show every row and column of the first one's products."""
+    from paper_2608_24204_amd.binding import WiciModel
+    cfg, w, w64 = setup(name, "bf16")
+    sizes = TILE_ROWS[name]
+    toks = np.random.default_rng(8).integers(0, cfg.vocab, sizes[-1]).astype(np.int32)
+    orc = DecoderOracle(cfg, w64, max_seq=sizes[-1])
+    ref = orc.full(toks)
+    m = WiciModel(cfg, max_seq=sizes[-1], prefill_chunk=2048)
+    try:
+        m.load_weights(w)
+        for n in sizes:
+            m.reset_kv()
+            tok, lg = m.prefill(toks[:n], want_logits=True)
+            print(f"[rows] {name} {n} rows: {inf_rel(lg, ref[n - 1]):.2e}", flush=True)
             assert inf_rel(lg, ref[n - 1]) <= 1e-3, n
             check_kv(m, orc, n)
     finally:

@@ -12,7 +12,7 @@ import subprocess
 import numpy as np
 import pytest
 
-from tests.test_gpu_rows import CFGS
+from tests.test_gpu_rows import CFGS, TILE_CFGS, TILE_ROWS
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 GXX = shutil.which("g++")
@@ -153,6 +153,23 @@ def prompt_products(ask, cfg, M, chunk=2048):
             s = ask([(kind(name == "gu"), BF16, nt, M, N, K, n)])[0][0]
             out[name] = (TILES[s], n, N, K)
     return out
+
+
+def test_ragged_tile_prompts_reach_every_tile_and_epilogue(ask):
+    """What test_ragged_tiles_match_oracle says of its configurations: every tile with
+    stored, residual, SwiGLU and K-range results, at a row remainder and a column remainder
+    (a SwiGLU product has whole 128-column tiles always)."""
+    seen = set()
+    for name, sizes in TILE_ROWS.items():
+        for M in sizes:
+            for p, (tile, n, N, K) in prompt_products(ask, TILE_CFGS[name], M).items():
+                if tile not in TILES:
+                    continue
+                bm, bn = map(int, tile.split("x"))
+                what = "ranges" if n > 1 else {"qkv": "store", "gu": "swiglu"}.get(p, "resid")
+                if M % bm and (N % bn or (what == "swiglu" and bn == 128)):
+                    seen.add((what, tile))
+    assert seen == {(w, t) for w in ("store", "resid", "swiglu", "ranges") for t in TILES}
 
 
 def test_odd_depths_reach_the_other_kernels(ask):
