@@ -26,10 +26,11 @@
  *    server thread, as in the paper's context management, Sec. "WiCi Library").
  *  - Device memory is owned by the caller (see wici_bind_memory); the library
  *    owns only host state, captured decode graphs (the per-token step, and the
- *    batched step per batch size it led) and a 16-byte pinned, device-mapped
+ *    batched step per batch size it led) and a 20-byte pinned, device-mapped
  *    host buffer into which each step's last kernel writes the step state (read
- *    by the host after the stream drains), and, once it has led a batched step, 18 KB
- *    of the same for that step's descriptors and states, all released by wici_destroy.
+ *    by the host once that kernel has set its `done`), and, once it has led a batched
+ *    step, 17 KB of the same for that step's descriptors and states, all released by
+ *    wici_destroy.
  */
 #ifndef WICI_H
 #define WICI_H

@@ -1025,6 +1025,9 @@ static hipError_t gemm_dma_launch(const ActBuf& A, int lda, const void* W, int M
   return hipGetLastError();
 }
 
+// (SwiGLU of three terms on 128 x 256 takes all 256 registers and spills 3, one of which
+// is read back every second step; 128 x 128, which spills none, takes 627 us against 616
+// at 1024 rows of 8B gate/up, 1254 against 1164 at 2048, 3217 against 2942 on 32B.)
 template <int NT, int EPI>
 static hipError_t gemm_dma_pick(const ActBuf& A, int lda, const void* W, int M, int N, int K,
                                 float* C, int ldc, const ActBuf& H, int ldh, hipStream_t st,

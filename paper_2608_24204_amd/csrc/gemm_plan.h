@@ -202,7 +202,8 @@ inline bool gemm_rows_best(int wt, int nt, int M, int N, int K, int most) {
 }
 
 // Whether it does where only the launch itself can add K ranges; the other choice is a
-// tiled product in one range.  Past 64 rows again not in more than one round (LM head of
+// tiled product in one range (up to 64 rows 8B QKV 18.9 and 52.9 us at 48, gate/up 47.4
+// and 58.6; LM head 239 and 246, but 286 and 264 at 64).  Past 64 rows again not in more than one round (LM head of
 // 128256 at 80 rows 348 and 309 us, at 128 477 and 341; 32B gate/up 175 and 160, 233 and
 // 179; 8B gate/up, one round, 74.3 and 87.9, 86.5 and 97.4), nor in K ranges where the
 // tiles, two to each of its 128 weight rows then, fill the chip (1B gate/up 30.4 and

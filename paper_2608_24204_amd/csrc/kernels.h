@@ -200,8 +200,9 @@ bool attn_group_supported(int G);
 // C[M, N] (ldc) = A[M, K] (lda) x W[N, K]^T with epilogue STORE / RESID (into C,
 // fp32) or SWIGLU (H[M, N/2] (ldh) = silu(gate) * up of the packed column pairs,
 // written as an activation buffer).  A.nt == 0: vector fp32 product (W bf16 or
-// fp32); A.nt = 1..3: matrix-core product of the nt bf16 planes with bf16 W.
-// K must be a multiple of 32 (64 for bf16 W and more than 32 rows).
+// fp32); A.nt = 1..3: matrix-core product of the nt bf16 planes with bf16 or Q8 W.
+// K must be a multiple of 32, on the matrix cores of 64 for Q8 W and for more than 32
+// rows.
 hipError_t launch_gemm(int wt, int epi, const ActBuf& A, int lda, const void* W, int M,
                        int N, int K, float* C, int ldc, const ActBuf& H, int ldh,
                        hipStream_t st);
