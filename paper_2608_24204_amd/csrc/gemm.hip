@@ -1123,8 +1123,8 @@ static hipError_t gemm_rows_launch(const ActBuf& A, int lda, const void* W, int 
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   hipLaunchKernelGGL(fn, dim3(grid), dim3(256), lds, st, A.planes, A.plane_stride, lda, W, M, N, K,
-                     nsplit, K / nsplit, C, c_split, ldc, H, ldh, reinterpret_cast<floatx4_t*>(part), sync,
-                     fault, drill, S);
+                     nsplit, K / nsplit, C, c_split, ldc, H, ldh,
+                     reinterpret_cast<floatx4_t*>(part), sync, fault, drill, S);
   return hipGetLastError();
 }
 
