@@ -663,6 +663,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   constexpr auto group = [](int n) { return n * (NT * TM + WN) * 4 + TM * WN * 4 <= 192; };
   constexpr int SG = Q8 ? (NT * TM <= 6 ? 4 : 2)
                      : group(KC / kBK) ? KC / kBK : group(2) ? 2 : 1;
+  // Up to 32 rows of bf16 weights a slice's products are summed by themselves and added to
+  // the earlier slices' sums while the next slice is read.  One fp32 sum over a whole K range
+  // put the keys and values of prompts of up to 16 rows 40% further from 64 bits than
+  // k_gemm_skinny's four over a quarter each (8B, three terms, 4.9e-7 against 3.6e-7; so
+  // 1.7e-7), and gate/up's results up to 32.  Times are the same up to 16 rows; at 17 to 32,
+  // where slices are 64 deep, three-term products take up to 4% more (8B QKV 13.4 -> 14.0 us,
+  // LM head 185 -> 189), gate/up of two terms 41.2 as before.  (From 33 rows the tiles' sums
+  // were no shorter, and it would cost 3 to 7%.)
+  constexpr bool BLK = !Q8 && TM <= 2;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
 
   const int T = (N + BN - 1) / BN;
@@ -720,9 +729,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < WN; ++j) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  floatx4_t blk[TM][WN];  // BLK: the last slice's sums, not yet in acc
+  auto fold = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][j][r] += blk[i][j][r];
+  };
+  if constexpr (BLK) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < WN; ++j) blk[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  }
   auto compute = [&](int stage) {
     const bf16_t* sb = smem + stage * STAGE;
     const bf16_t* xb = sb + WUNITS * 8;
+    if constexpr (BLK) fold();
     u32x2_t sc[WN];
     if constexpr (Q8) {
 #pragma unroll
@@ -800,9 +825,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
-              for (int j = 0; j < WN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[u][i][p], wf[u][j], acc[i][j],
-                                                                    0, 0, 0);
+              for (int j = 0; j < WN; ++j) {
+                floatx4_t& c = BLK ? blk[i][j] : acc[i][j];
+                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    xf[u][i][p], wf[u][j],
+                    BLK && s0 + u + p == 0 ? floatx4_t{0.f, 0.f, 0.f, 0.f} : c, 0, 0, 0);
+              }
       }
     }
   };
@@ -818,6 +846,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if (kt + STG - 1 < KT) issue((kt + STG - 1) % STG, kt + STG - 1);
     compute(kt % STG);
   }
+  if constexpr (BLK) fold();
 
   auto out_row = [&](int i, int r) { return i * 16 + 4 * g + r; };
   auto out_col = [&](int j) { return n0 + (wave * WN + j) * 16 + fr; };
@@ -1196,7 +1225,7 @@ static hipError_t gemm_split_nt(int wt, const ActBuf& A, int lda, const void* W,
                                 int K, int nsplit, float* P, size_t p_split, hipStream_t st) {
   const ActBuf none{};
   if (gemm_rows_best(wt, NT, M, N, K, nsplit)) {
-    const RowsPlan p = rows_plan(wt, GEMV_STORE, M, N, K, ~(size_t)0, nsplit);
+    const RowsPlan p = rows_plan(wt, GEMV_STORE, M, N, K, kAddedOutside, nsplit);
     return p.nsplit == nsplit
                ? gemm_rows_wt<NT, GEMV_STORE>(wt, p, A, lda, W, M, N, K, P, p_split, N, none, 0,
                                               nullptr, nullptr, nullptr, st, false)

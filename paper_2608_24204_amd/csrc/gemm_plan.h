@@ -155,7 +155,9 @@ inline int gemm_rows_splits(int tm, int bn, int N, int K, size_t part_floats, in
   return best;
 }
 
-// 16-row tiles, 64-row column tiles per workgroup and K ranges of the few-rows kernel.
+// 16-row tiles, 64-row column tiles per workgroup and K ranges of the few-rows kernel;
+// part_floats is kAddedOutside where another kernel adds the ranges.
+constexpr size_t kAddedOutside = ~(size_t)0;
 struct RowsPlan {
   int tm, wn, nsplit;
 };
@@ -196,7 +198,7 @@ inline RowsPlan rows_plan(int wt, int epi, int M, int N, int K, size_t part_floa
 inline bool gemm_rows_best(int wt, int nt, int M, int N, int K, int most) {
   if (!gemm_rows_takes(wt, nt, M, K)) return false;
   if (M <= 64) return true;
-  const RowsPlan p = rows_plan(wt, GEMV_STORE, M, N, K, ~(size_t)0, M <= 96 ? most : 1);
+  const RowsPlan p = rows_plan(wt, GEMV_STORE, M, N, K, kAddedOutside, M <= 96 ? most : 1);
   const int wgs = (N + 64 * p.wn - 1) / (64 * p.wn) * p.nsplit;
   return wgs >= 192 && wgs <= 256;
 }
@@ -218,7 +220,7 @@ inline bool gemm_rows_merge_best(int wt, int nt, int M, int N, int K) {
 // split): of the few-row kernel where that is the best one, of the tiles otherwise.
 inline int gemm_split_count(int wt, int nt, int M, int N, int K, int max_split) {
   return gemm_rows_best(wt, nt, M, N, K, max_split)
-             ? rows_plan(wt, GEMV_STORE, M, N, K, ~(size_t)0, max_split).nsplit
+             ? rows_plan(wt, GEMV_STORE, M, N, K, kAddedOutside, max_split).nsplit
              : tile_split_count(wt, nt, M, N, K, max_split);
 }
 

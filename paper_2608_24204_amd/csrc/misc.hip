@@ -446,18 +446,13 @@ static bool rope_append4(float* qkv, int T, int p0, int Hq, const float* cos_t,
       hipLaunchKernelGGL((k_rope_append4<KT, 1, MAXI>), dim3(T), dim3(256), 0, st, qkv, p0, Hq,
                          cos_t, sin_t, kv, (const float*)nullptr, p_split);
       return true;
-    case 2:
-      hipLaunchKernelGGL((k_rope_append4<KT, 2, MAXI>), dim3(T), dim3(256), 0, st, qkv, p0, Hq,
-                         cos_t, sin_t, kv, part, p_split);
-      return true;
-    case 3:
-      hipLaunchKernelGGL((k_rope_append4<KT, 3, MAXI>), dim3(T), dim3(256), 0, st, qkv, p0, Hq,
-                         cos_t, sin_t, kv, part, p_split);
-      return true;
-    case 4:
-      hipLaunchKernelGGL((k_rope_append4<KT, 4, MAXI>), dim3(T), dim3(256), 0, st, qkv, p0, Hq,
-                         cos_t, sin_t, kv, part, p_split);
-      return true;
+#define WICI_RA(NP)                                                                             \
+  case NP:                                                                                      \
+    hipLaunchKernelGGL((k_rope_append4<KT, NP, MAXI>), dim3(T), dim3(256), 0, st, qkv, p0, Hq,  \
+                       cos_t, sin_t, kv, part, p_split);                                        \
+    return true;
+    WICI_RA(2) WICI_RA(3) WICI_RA(4) WICI_RA(5) WICI_RA(6) WICI_RA(7) WICI_RA(8)
+#undef WICI_RA
     default:
       return false;
   }

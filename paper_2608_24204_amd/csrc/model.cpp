@@ -32,8 +32,8 @@ constexpr int kMaxBatch = 256;  // sequences per batched decode step
 constexpr size_t kFuseRopeMaxBlocks = 3 * 4 * 256;  // see enqueue_decode_batch
 constexpr int kMaxKSplit = 4;   // K ranges of a prefill residual product of whole chunks
                                 // (partials kept; more ranges for fewer rows)
-constexpr int kMaxRowSplit = 8; // partials the row norms add, and the RoPE + append
-constexpr int kMaxRopeSplit = 4;
+constexpr int kMaxRowSplit = 8; // partials the row norms add, and the RoPE + append of up to
+constexpr int kMaxRopeSplit = 4;  // 64 rows, and of more
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 size_t dsize(int32_t dt) { return dt == WICI_BF16 ? 2 : 4; }
@@ -440,7 +440,7 @@ hipError_t enqueue_prefill_chunk(wici_model* m, int p0, int T, int tok_off) {
   // the QKV projection too, as far as its partials fit the split buffer; they are
   // added (in range order) by the RoPE + append kernel.  Measured at 1024 rows
   // (8B): 185 -> 164 us; at 512 rows (1B): 56 -> 33 us.
-  const int s_q = splits(rd(a, pl.qkv).nt, nqkv, d, kMaxRopeSplit);
+  const int s_q = splits(rd(a, pl.qkv).nt, nqkv, d, T <= 64 ? kMaxRowSplit : kMaxRopeSplit);
   const size_t q_split = (size_t)T * nqkv;
   int pending = 0;  // splits of the previous down product not yet added to x
   // (the normalised rows are written with as many terms as their product reads)

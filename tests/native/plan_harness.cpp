@@ -19,7 +19,7 @@ int main() {
       std::printf("%d %d %d\n", c, gemm_rows_best(wt, nt, M, N, K, n),
                   gemm_rows_best(wt, nt, M, N, K, c));
     } else if (!std::strcmp(what, "rows")) {  // the few-row launch of a product in at most n ranges
-      const RowsPlan p = rows_plan(wt, GEMV_STORE, M, N, K, ~(size_t)0, n);
+      const RowsPlan p = rows_plan(wt, GEMV_STORE, M, N, K, kAddedOutside, n);
       std::printf("%d %d %d\n", p.tm, p.wn, p.nsplit);
     } else if (!std::strcmp(what, "merge")) {
       std::printf("%d\n", gemm_rows_merge_best(wt, nt, M, N, K));

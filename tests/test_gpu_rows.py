@@ -248,3 +248,34 @@ def test_prompts_have_no_in_launch_sum(cuda_ok, name, weights):
 
     for (t0, l0), (t1, l1) in zip(run(False), run(True)):
         assert t0 == t1 and np.array_equal(l0, l1)
+
+
+@pytest.mark.parametrize("n", [2, 16, 17, 32])
+def test_short_prompts_sum_in_quarters_of_k(cuda_ok, n):
+    """Three terms throughout and an fp32 cache: what is left is the error of fp32 sums.  m
+    additions in a row, each rounded to u = 2^-24 of a partial sum that grows as a random
+    walk, are u sqrt(m / 6) off.  Over a quarter of K = 4096 (m = 3 * 1024 / 32 matrix-core
+    steps) that is 4.0 u, 2.4e-7, over all of it 4.8e-7; the norm, the rotation and the
+    dropped terms are about as much again as the former: 5.7 u in all, bound 6.7 u, and
+    three times that behind the layer's other three products."""
+    from paper_2608_24204_amd.binding import WiciModel
+    cfg = configs.ModelConfig(name="t_sums", key=119, n_layers=2, d_model=4096, n_heads=32,
+                              n_kv_heads=8, head_dim=128, ffn_dim=2048, vocab=1003,
+                              kv_dtype="f32")
+    w = inputs.make_weights(cfg, gain_std=0.1)
+    toks = np.random.default_rng(9).integers(0, cfg.vocab, n).astype(np.int32)
+    orc = DecoderOracle(cfg, inputs.weights_f64(cfg, w), max_seq=n)
+    orc.full(toks)
+    m = WiciModel(cfg, max_seq=n, prefill_mode="bf16x3")
+    try:
+        m.load_weights(w)
+        m.prefill(toks)
+        err = []
+        for l in range(2):
+            got = np.concatenate([z.reshape(n, -1) for z in m.read_kv(l, 0, n)]).astype(np.float64)
+            want = np.concatenate([z[:n].reshape(n, -1) for z in (orc.K[l], orc.V[l])])
+            err.append(np.linalg.norm(got - want) / np.linalg.norm(want))
+        print(f"[rows] sums {n} rows: keys and values {err[0]:.2e} {err[1]:.2e}", flush=True)
+        assert err[0] <= 6.7 * 2.0 ** -24 and err[1] <= 20 * 2.0 ** -24
+    finally:
+        m.close()
